@@ -27,7 +27,20 @@
 // |da|, |db| <= R, at (db + R)(2R + 1) + (da + R); for the peridynamic kernel
 // each entry is a 2x2 block stored [row component][window][column component].
 //
-// One workgroup per row.  The partner triangles F of the search squares of
+// Every row is the same row (k_asm_pairs, k_asm_row, k_asm_copy).  The mesh is
+// uniform and gamma depends on x - y only, so an integral over (E, F) depends
+// on the offset between the two triangles, not on where they lie: the windows
+// of two nodes are equal whenever neither node's partners are cut off by the
+// end of the mesh.  A collar of at least R1 cells (the partner search radius)
+// keeps every row whole; the row is then integrated once, its pairs spread
+// over the chip, and stored (n - 1)^2 times.  Shorter collars cut the rows of
+// the outer nodes differently, and very small meshes have no room for the pair
+// shares in their own windows: those are integrated row by row (k_assemble_2d).
+// Measured on the fractional system (h = 1/96, delta = 0.1, 9 025 rows of 45 MB):
+// 14.1 ms row by row (FP64 arithmetic), 27 us once for all (launches and the
+// stores).
+//
+// Row by row: one workgroup per row.  The partner triangles F of the search squares of
 // the elements E holding the row's node are spread over the threads in a
 // fixed stride; each thread integrates its pair into registers.  Every sum
 // has a fixed order, so the windows are the same bits from run to run:
@@ -45,6 +58,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 namespace dd {
@@ -90,13 +104,14 @@ inline void asm_disk(AsmProblem &P, double delta) {
 
 // Quadrature rules on the reference triangle: barycentric points and weights
 // (summing to 1), {l0, l1, l2, w} per point; rows 0-6 the 7-point rule,
-// rows 7-12 the 6-point rule.  Filled from the host (asm_rule_table) before
-// each launch; read with uniform indices (scalar loads).
-__constant__ double c_asm_rule[13][4];
-
-inline void asm_rule_table(double t[13][4]) {
+// rows 7-12 the 6-point rule.  Read with uniform indices (scalar loads) or, in
+// k_asm_pairs, one row per lane.
+struct AsmRules { double t[13][4]; };
+constexpr AsmRules asm_rule_table() {
+  AsmRules r{};
+  auto &t = r.t;
   // 7 points, degree 5: centroid and two 3-point orbits (a, a, b)
-  const double q15 = std::sqrt(15.0);
+  const double q15 = 3.872983346207417;     // sqrt(15)
   const double oa[2] = {(6.0 - q15) / 21.0, (6.0 + q15) / 21.0};
   const double ob[2] = {(9.0 + 2.0 * q15) / 21.0, (9.0 - 2.0 * q15) / 21.0};
   const double ow[2] = {(155.0 - q15) / 1200.0, (155.0 + q15) / 1200.0};
@@ -117,7 +132,10 @@ inline void asm_rule_table(double t[13][4]) {
       for (int j = 0; j < 3; ++j) t[q][j] = ((j + k) % 3 == 2) ? 1.0 - 2.0 * cc[o] : cc[o];
       t[q][3] = cw[o];
     }
+  return r;
 }
+__constant__ AsmRules c_asm_rules = asm_rule_table();
+
 
 // Barycentric coordinate k (0..2; -1: the vertex is not in the triangle) of
 // a point with coordinates l0, l1, l2 (per-lane index, uniform values).
@@ -154,11 +172,11 @@ __device__ __forceinline__ void asm_pair(const AsmProblem &P, const double Ex[3]
   double bm[NE];                         // the row node's coordinate at E's points
 #pragma unroll
   for (int q = 0; q < NE; ++q)
-    bm[q] = asm_sel(mE, c_asm_rule[QE + q][0], c_asm_rule[QE + q][1], c_asm_rule[QE + q][2]);
+    bm[q] = asm_sel(mE, c_asm_rules.t[QE + q][0], c_asm_rules.t[QE + q][1], c_asm_rules.t[QE + q][2]);
 #pragma unroll 1
   for (int p = 0; p < NF; ++p) {
-    const double ly0 = c_asm_rule[QF + p][0], ly1 = c_asm_rule[QF + p][1], ly2 = c_asm_rule[QF + p][2];
-    const double wp = c_asm_rule[QF + p][3] * cst;
+    const double ly0 = c_asm_rules.t[QF + p][0], ly1 = c_asm_rules.t[QF + p][1], ly2 = c_asm_rules.t[QF + p][2];
+    const double wp = c_asm_rules.t[QF + p][3] * cst;
     const double am = asm_sel(mF, ly0, ly1, ly2);
     double au[6];
 #pragma unroll
@@ -170,9 +188,9 @@ __device__ __forceinline__ void asm_pair(const AsmProblem &P, const double Ex[3]
     }
 #pragma unroll
     for (int q = 0; q < NE; ++q) {
-      const double lx[3] = {c_asm_rule[QE + q][0], c_asm_rule[QE + q][1], c_asm_rule[QE + q][2]};
+      const double lx[3] = {c_asm_rules.t[QE + q][0], c_asm_rules.t[QE + q][1], c_asm_rules.t[QE + q][2]};
       const double dm = am - bm[q];
-      const double w = c_asm_rule[QE + q][3] * wp;
+      const double w = c_asm_rules.t[QE + q][3] * wp;
       double g = 0.0, s0 = 0.0, s1 = 0.0, b00 = 0.0, b01 = 0.0, b11 = 0.0;
       if constexpr (KER == kKerConst) {
         g = w * dm;
@@ -436,6 +454,274 @@ __global__ void __launch_bounds__(kAsmBlock, AsmShape<KER>::kWaves) k_assemble_2
     }
     out[i] = v;
   }
+}
+
+// ------------------------------------------- one row for all (uniform mesh) --
+// Elements holding the row's node, placed at the origin: element e has
+// triangle type e & 1 in cell (asm_ea(e), asm_eb(e)).
+constexpr int kAsmElems = 6;
+__device__ __forceinline__ int asm_ea(int e) { return e < 3 ? -1 : 0; }
+__device__ __forceinline__ int asm_eb(int e) { return e < 2 || e == 3 ? -1 : 0; }
+
+// Share values of one (E, F) pair: NV for each vertex of E, then NV for each
+// vertex of F outside E (zeros for shared ones).
+template <int KER> struct AsmShares { static constexpr int N = 6 * AsmShape<KER>::NV; };
+
+// Point `ly` of F (weight wp with every constant factor) against the points
+// q0, q0 + kAsmSplit, ... of the NE points of E's rule (rows QE ..): shares
+// added to acc.  eF[u]: index in F of E's vertex u, or -1.
+constexpr int kAsmSplit = 4;
+template <int KER, int QE, int NE>
+__device__ __forceinline__ void asm_point(const AsmProblem &P, const double (&Ex)[3], const double (&Ey)[3],
+                                          const double (&Fx)[3], const double (&Fy)[3], int mE, int mF,
+                                          const int (&eF)[3], int q0, const double *ly, double scale,
+                                          double (&acc)[AsmShares<KER>::N]) {
+  constexpr int NV = AsmShape<KER>::NV;
+  const double ly0 = ly[0], ly1 = ly[1], ly2 = ly[2], wp = scale * ly[3];
+  const double am = asm_sel(mF, ly0, ly1, ly2);
+  double au[3];
+#pragma unroll
+  for (int u = 0; u < 3; ++u) au[u] = asm_sel(eF[u], ly0, ly1, ly2);
+  const double y0 = ly0 * Fx[0] + ly1 * Fx[1] + ly2 * Fx[2];
+  const double y1 = ly0 * Fy[0] + ly1 * Fy[1] + ly2 * Fy[2];
+  double gs[NV];                          // sums over E's points of the pair weights
+#pragma unroll
+  for (int c = 0; c < NV; ++c) gs[c] = 0.0;
+#pragma unroll
+  for (int i = 0; i < (NE + kAsmSplit - 1) / kAsmSplit; ++i) {
+    const int q = q0 + kAsmSplit * i;
+    const double *rx = c_asm_rules.t[QE + (q < NE ? q : 0)];
+    const double lx[3] = {rx[0], rx[1], rx[2]};
+    const double dm = am - asm_sel(mE, lx[0], lx[1], lx[2]);
+    const double w = q < NE ? rx[3] * wp : 0.0;
+    double g[NV];
+    g[0] = w * dm;
+    if constexpr (KER != kKerConst) {
+      const double s0 = lx[0] * Ex[0] + lx[1] * Ex[1] + lx[2] * Ex[2] - y0;
+      const double s1 = lx[0] * Ey[0] + lx[1] * Ey[1] + lx[2] * Ey[2] - y1;
+      const double r2 = s0 * s0 + s1 * s1;
+      // (r2 = 0 only where the points coincide, where d_m = 0 as well)
+      double f = 0.0;
+      if (r2 > 0.0) {
+        if constexpr (KER == kKerPD) f = w * dm / (r2 * sqrt(r2));
+        else f = w * dm * exp2(-(1.0 + P.s) * log2(r2));   // |x - y|^-(2 + 2s)
+      }
+      g[0] = f;
+      if constexpr (KER == kKerPD) {
+        g[0] = f * s0 * s0;
+        g[1] = f * s0 * s1;
+        g[2] = f * s1 * s1;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      gs[c] += g[c];
+#pragma unroll
+      for (int u = 0; u < 3; ++u) acc[u * NV + c] += (au[u] - lx[u]) * g[c];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < NV; ++c) {          // F's vertices: lambda_j(y) for every point of E
+    acc[(3 + 0) * NV + c] += ly0 * gs[c];
+    acc[(3 + 1) * NV + c] += ly1 * gs[c];
+    acc[(3 + 2) * NV + c] += ly2 * gs[c];
+  }
+}
+
+// The shares of every (E, F) pair of the row of a node at the origin: pair
+// e per_e + f (partner candidate f of element e) in column `pair` of share,
+// [value][pair].  32 lanes per pair: lane 4 p + q takes point p of F's rule and
+// every fourth point of E's, q first, and a butterfly adds the lanes up.  Bound:
+// the latency of a lane's chain (a logarithm and an exponential per point pair);
+// eight lanes per pair, one per point of F, took 16 us on the fractional system
+// (h = 1/96, 6 348 candidates), 32 lanes 9 us.
+constexpr int kAsmLanes = 8 * kAsmSplit;
+template <int KER>
+__global__ void __launch_bounds__(kAsmBlock) k_asm_pairs(AsmProblem P, double *__restrict__ share) {
+  constexpr int NV = AsmShape<KER>::NV, NS = AsmShares<KER>::N;
+  const int span = 2 * P.R1 + 1, per_e = span * span * 2, np = kAsmElems * per_e;
+  const int pair = (blockIdx.x * kAsmBlock + threadIdx.x) / kAsmLanes;
+  const int lane = threadIdx.x % kAsmLanes, p = lane / kAsmSplit, q0 = lane % kAsmSplit;
+  if (pair >= np) return;                 // (whole groups of lanes)
+  const int e = pair / per_e, f = pair - e * per_e;
+  int ea[3], eb[3], fa[3], fb[3];
+  asm_tri(asm_ea(e), asm_eb(e), e & 1, ea, eb);
+  const int cell = f >> 1;
+  asm_tri(asm_ea(e) - P.R1 + cell % span, asm_eb(e) - P.R1 + cell / span, f & 1, fa, fb);
+  const int dA = (ea[0] + ea[1] + ea[2]) - (fa[0] + fa[1] + fa[2]);
+  const int dB = (eb[0] + eb[1] + eb[2]) - (fb[0] + fb[1] + fb[2]);
+  const bool in = (long long)(dA * dA + dB * dB) <= P.thr;
+  double acc[NS];
+#pragma unroll
+  for (int k = 0; k < NS; ++k) acc[k] = 0.0;
+  bool dup[3] = {false, false, false};
+  if (in) {
+    int eF[3] = {-1, -1, -1}, mE = 0, mF = -1;
+    bool touching = false;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      if (ea[j] == 0 && eb[j] == 0) mE = j;
+      if (fa[j] == 0 && fb[j] == 0) mF = j;
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+        if (fa[j] == ea[u] && fb[j] == eb[u]) {
+          eF[u] = j;
+          dup[j] = touching = true;
+        }
+    }
+    double Ex[3], Ey[3], Fx[3], Fy[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      Ex[j] = ea[j] * P.h;
+      Ey[j] = eb[j] * P.h;
+      Fx[j] = fa[j] * P.h;
+      Fy[j] = fb[j] * P.h;
+    }
+    const double area = 0.5 * P.h * P.h;
+    const double cst = area * area * P.phi * (mF >= 0 ? 1.0 : 2.0);    // (F, E) folded in
+    if (KER == kKerFrac && touching) {
+      if (p < 6)
+        asm_point<KER, 0, 7>(P, Ex, Ey, Fx, Fy, mE, mF, eF, q0, c_asm_rules.t[7 + p], 0.5 * cst, acc);
+      if (p < 7) asm_point<KER, 7, 6>(P, Ex, Ey, Fx, Fy, mE, mF, eF, q0, c_asm_rules.t[p], 0.5 * cst, acc);
+    } else if (p < 7) {
+      asm_point<KER, 0, 7>(P, Ex, Ey, Fx, Fy, mE, mF, eF, q0, c_asm_rules.t[p], cst, acc);
+    }
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+#pragma unroll
+      for (int o = kAsmLanes / 2; o >= 1; o >>= 1) acc[k] += __shfl_xor(acc[k], o);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 6; ++v)             // lane v stores vertex v's share
+    if (lane == v)
+#pragma unroll
+      for (int c = 0; c < NV; ++c) share[(size_t)(v * NV + c) * np + pair] = v >= 3 && dup[v - 3] ? 0.0 : acc[v * NV + c];
+}
+
+// The window of the row from the pair shares, entry by entry: node (da, db)
+// collects, over the six elements E, the shares of the six triangles F around
+// it in which it is a vertex outside E; the seven nodes that are vertices of
+// some E also the sums over all partners of that E (a workgroup each: blocks
+// 0 .. 6).  Fixed order throughout.  Bound: load latency (10 us at h = 1/96).
+constexpr int kAsmNear = 7;
+template <int KER>
+__global__ void __launch_bounds__(kAsmBlock) k_asm_row(AsmProblem P, const double *__restrict__ share,
+                                                       double *__restrict__ row) {
+  constexpr int NC = AsmShape<KER>::NC, NV = AsmShape<KER>::NV;
+  const int span = 2 * P.R1 + 1, per_e = span * span * 2, np = kAsmElems * per_e;
+  const int W2 = P.W * P.W;
+  const bool near_blk = blockIdx.x < kAsmNear;
+  // node (da, db); block k < 7 takes the k-th node of the row's elements
+  constexpr int na[kAsmNear] = {-1, 0, -1, 0, 1, 0, 1}, nb[kAsmNear] = {-1, -1, 0, 0, 0, 1, 1};
+  int da, db, wi;
+  if (near_blk) {
+    da = na[blockIdx.x];
+    db = nb[blockIdx.x];
+    wi = (db + P.R) * P.W + da + P.R;
+  } else {
+    wi = ((int)blockIdx.x - kAsmNear) * kAsmBlock + threadIdx.x;
+    if (wi >= W2) return;
+    db = wi / P.W - P.R;
+    da = wi - (db + P.R) * P.W - P.R;
+    // (da, db) is a near node when it lies in the hexagon of the six elements
+    if (da >= -1 && da <= 1 && db >= -1 && db <= 1 && da - db <= 1 && db - da <= 1) return;
+  }
+  double v[NV];
+#pragma unroll
+  for (int c = 0; c < NV; ++c) v[c] = 0.0;
+  // pair of element e and the triangle t that has the node as vertex j
+  // (asm_tri), or -1 where it is no candidate
+  auto gather = [&](int e, int t, int j) {
+    const int fa = da - (j == 0 ? 0 : (j == 1 ? 1 : 1 - t)), fb = db - (j == 0 ? 0 : (j == 1 ? t : 1));
+    const int x = fa - asm_ea(e) + P.R1, y = fb - asm_eb(e) + P.R1;
+    if (x < 0 || y < 0 || x >= span || y >= span) return;
+    const int pair = e * per_e + 2 * (y * span + x) + t;
+#pragma unroll
+    for (int c = 0; c < NV; ++c) v[c] += share[(size_t)((3 + j) * NV + c) * np + pair];
+  };
+  if (!near_blk) {
+#pragma unroll
+    for (int e = 0; e < kAsmElems; ++e)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) gather(e, t, j);
+  } else {
+    if (threadIdx.x < kAsmElems * 6) gather(threadIdx.x / 6, threadIdx.x % 2, threadIdx.x % 6 / 2);
+    constexpr int U = 4;                  // loads in flight
+    for (int e = 0; e < kAsmElems; ++e) {
+      int ea[3], eb[3], u = -1;
+      asm_tri(asm_ea(e), asm_eb(e), e & 1, ea, eb);
+      for (int j = 0; j < 3; ++j)
+        if (ea[j] == da && eb[j] == db) u = j;
+      if (u < 0) continue;
+      for (int f0 = threadIdx.x; f0 < per_e; f0 += U * kAsmBlock) {
+        double w[U][NV];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+          for (int c = 0; c < NV; ++c) {
+            const int f = f0 + k * kAsmBlock;
+            w[k][c] = f < per_e ? share[(size_t)(u * NV + c) * np + e * per_e + f] : 0.0;
+          }
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+          for (int c = 0; c < NV; ++c) v[c] += w[k][c];
+      }
+    }
+    __shared__ double part[kAsmWaves][NV];
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      for (int o = 32; o >= 1; o >>= 1) v[c] += __shfl_xor(v[c], o);
+      if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][c] = v[c];
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      v[c] = part[0][c];
+      for (int w = 1; w < kAsmWaves; ++w) v[c] += part[w][c];
+    }
+  }
+  if constexpr (NC == 1) {
+    row[wi] = v[0];
+  } else {                                // [row comp][window][column comp], [1][0] equal to [0][1]
+    row[2 * wi] = v[0];
+    row[2 * wi + 1] = v[1];
+    row[2 * (W2 + wi)] = v[1];
+    row[2 * (W2 + wi) + 1] = v[2];
+  }
+}
+
+// Rows 1 .. nrows - 1 of win (WW values each) := row 0.  A thread keeps one
+// value and stores it to its share of the rows; a wave's stores are 512
+// contiguous bytes.  Bound: HBM writes (45 MB in 8.8 us at h = 1/96).
+__global__ void __launch_bounds__(kAsmBlock) k_asm_copy(int nrows, int WW, double *__restrict__ win) {
+  const int i = blockIdx.x * kAsmBlock + threadIdx.x;
+  if (i >= WW) return;
+  const double v = win[i];
+  for (int r = 1 + blockIdx.y; r < nrows; r += gridDim.y) win[(size_t)r * WW + i] = v;
+}
+
+// Launches the three on st; returns false (nothing launched) where the rows
+// differ or the pair shares, which live in rows 1 .. until the copy overwrites
+// them, do not fit.
+template <int KER>
+bool launch_asm_uniform(const AsmProblem &P, double *win, hipStream_t st) {
+  constexpr int NC = AsmShape<KER>::NC;
+  const int span = 2 * P.R1 + 1, np = kAsmElems * span * span * 2;
+  const int nrows = (P.n - 1) * (P.n - 1), WW = P.W * P.W * NC;
+  if (P.c < P.R1 || (size_t)(nrows - 1) * WW < (size_t)AsmShares<KER>::N * np) return false;
+  double *share = win + WW;
+  hipLaunchKernelGGL(k_asm_pairs<KER>, dim3((np * kAsmLanes + kAsmBlock - 1) / kAsmBlock), dim3(kAsmBlock), 0, st, P,
+                     share);
+  hipLaunchKernelGGL(k_asm_row<KER>, dim3(kAsmNear + (P.W * P.W + kAsmBlock - 1) / kAsmBlock), dim3(kAsmBlock), 0, st,
+                     P, share, win);
+  const int gx = (WW + kAsmBlock - 1) / kAsmBlock, gy = std::max(1, std::min(nrows - 1, 4096 / gx));
+  hipLaunchKernelGGL(k_asm_copy, dim3(gx, gy), dim3(kAsmBlock), 0, st, nrows, WW, win);
+  return true;
 }
 
 }  // namespace dd

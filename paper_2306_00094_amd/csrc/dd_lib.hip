@@ -2779,22 +2779,15 @@ dd_status dd_assemble_2d(int32_t n, int32_t collar, double delta, int32_t kernel
   const size_t lds = (size_t)kAsmWaves * P.WC * (kernel == kKerPD ? AsmShape<kKerPD>::NV : 1) * sizeof(double);
   if (lds > 65536) return fail(nullptr, DD_EINVAL, "window copies of more than 64 KiB per row");
   hipStream_t st = (hipStream_t)hip_stream;
-  static double rules[13][4];             // static: the copy below may run after the return
-  static bool rules_set = false;
-  if (!rules_set) {
-    asm_rule_table(rules);
-    rules_set = true;
-  }
-  hipError_t ec = hipMemcpyToSymbolAsync(HIP_SYMBOL(c_asm_rule), rules, sizeof(rules), 0,
-                                         hipMemcpyHostToDevice, st);
-  if (ec != hipSuccess) return fail(nullptr, DD_EHIP, std::string("quadrature rules: ") + hipGetErrorString(ec));
   const dim3 grid((unsigned)((n - 1) * (n - 1))), block(kAsmBlock);
-  if (kernel == kKerConst)
-    hipLaunchKernelGGL(k_assemble_2d<kKerConst>, grid, block, lds, st, P, win_dev);
-  else if (kernel == kKerFrac)
-    hipLaunchKernelGGL(k_assemble_2d<kKerFrac>, grid, block, lds, st, P, win_dev);
-  else
-    hipLaunchKernelGGL(k_assemble_2d<kKerPD>, grid, block, lds, st, P, win_dev);
+  auto launch = [&](auto ker) {
+    constexpr int K = decltype(ker)::value;
+    if (!launch_asm_uniform<K>(P, win_dev, st))
+      hipLaunchKernelGGL(k_assemble_2d<K>, grid, block, lds, st, P, win_dev);
+  };
+  if (kernel == kKerConst) launch(std::integral_constant<int, kKerConst>{});
+  else if (kernel == kKerFrac) launch(std::integral_constant<int, kKerFrac>{});
+  else launch(std::integral_constant<int, kKerPD>{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(nullptr, DD_EHIP, std::string("k_assemble_2d: ") + hipGetErrorString(e));
   return DD_OK;

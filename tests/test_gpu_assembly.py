@@ -92,3 +92,33 @@ def test_device_assembly_feeds_the_solver():
     u_gen = oracle.monolithic_solve(wl.asm.A, b)
     u_dev = oracle.monolithic_solve(A_dev, b)
     assert oracle.rel_err(u_dev, u_gen).max() <= 1e-10
+
+
+@pytest.mark.parametrize("kernel", [0, 1, 2])
+@pytest.mark.parametrize("n,delta,collar,extra", [
+    (24, 0.15, 5, 0),    # a collar as wide as the partner search: one row serves all
+    (24, 0.15, 4, 0),    # one cell short: integrated row by row
+    (24, 0.15, 9, 3),    # a wide collar and window
+    (3, 0.4, 3, 0),      # too few rows to hold the pair shares
+    (9, 0.05, 2, 1),     # horizon below the mesh width
+])
+def test_device_assembly_collars(kernel, n, delta, collar, extra):
+    """The row integrated once and stored for every node, and the rows
+    integrated one by one where the collar cuts them, against the generator on
+    the same mesh (same gate as above, for the same sums)."""
+    dd = _dd()
+    import ctypes
+    R = int(np.ceil(delta * n)) + 2 + extra
+    rowlen = (2 * R + 1) ** 2 * (4 if kernel == 2 else 1)
+    print(f"case assembly collar kernel={kernel} n={n} collar={collar} R={R}", flush=True)
+    ref = np.zeros((n - 1) ** 2 * rowlen)
+    rc = workloads._load().nl_assemble_2d(n, collar, delta, kernel, 1.7, 0.5, R, 4,
+                                          ref.ctypes.data_as(ctypes.POINTER(ctypes.c_double)))
+    assert rc == 0
+    win = torch.full((ref.size,), float("nan"), dtype=torch.float64, device="cuda")
+    dd.dd_assemble_2d(n, collar, delta, kernel, 1.7, 0.5, R, win)
+    torch.cuda.synchronize()
+    got, ref = win.cpu().numpy().reshape(-1, rowlen), ref.reshape(-1, rowlen)
+    scale = np.abs(ref).max(axis=1, keepdims=True)
+    assert np.all(scale > 0)
+    assert np.all(np.abs(got - ref) <= 1e-11 * scale)
