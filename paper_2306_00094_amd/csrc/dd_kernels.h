@@ -29,6 +29,12 @@ constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kRowsE = 64;    // rows per chunk in the element-wise kernels
 constexpr int kMaxLd = 64;    // widest right-hand-side batch
+// Second launch bound of the kernels with matrix instructions: two waves per
+// SIMD, so at most 256 registers a wave.  The compiler then keeps the
+// accumulators in ordinary registers; allowed all 512 it places them in the
+// accumulation half and copies them across around every use (32 moves per pass
+// of the unit loop of k_tile_rows).
+constexpr int kMfmaWaves = 2;
 
 __device__ __forceinline__ double tfma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float tfma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
@@ -2446,7 +2452,7 @@ __device__ __forceinline__ void store_coherent(T *p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <typename T, int OWN>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock, kMfmaWaves)
 k_potrf_flow(T *__restrict__ blocks, const long long *__restrict__ koff, const int *__restrict__ ni,
              int n_sub, int ntmax, int *__restrict__ status, unsigned *__restrict__ ticket,
              int *__restrict__ done, int *__restrict__ timeout, T *__restrict__ Xd, int spin) {
@@ -2645,7 +2651,7 @@ k_potrf_flow(T *__restrict__ blocks, const long long *__restrict__ koff, const i
 // Trailing update of panel J: A22 -= L21 L21^T on the 16x16 lower tiles of
 // every subdomain; grid (tile chunks, subdomains), one wave per tile.
 template <typename T>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock, kMfmaWaves)
 k_potrf_update(T *__restrict__ blocks, const long long *__restrict__ koff,
                const int *__restrict__ ni, int J, int use_mfma) {
   const int k = blockIdx.y;
@@ -2715,7 +2721,7 @@ k_potrf_update(T *__restrict__ blocks, const long long *__restrict__ koff,
 // B[l/16][l%16]; accumulator register r of lane l is row acc_row(g, r) of
 // column l%16, g = l/16.
 template <typename T>
-__global__ void __launch_bounds__(kWave)
+__global__ void __launch_bounds__(kWave, kMfmaWaves)
 k_trtri(const T *__restrict__ L, T *__restrict__ X, const long long *__restrict__ koff,
         const int *__restrict__ ni) {
   const int k = blockIdx.x, C = blockIdx.y;
@@ -2828,7 +2834,7 @@ k_trtri_diag(const T *__restrict__ L, T *__restrict__ X, const long long *__rest
 // per block row (before the four partial sums are combined) is enough.  The
 // partial sums alternate between two LDS buffers by block-row parity.
 template <typename T>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock, kMfmaWaves)
 k_trtri_panel(const T *__restrict__ L, T *__restrict__ X, const long long *__restrict__ koff,
               const int *__restrict__ ni) {
   typedef typename Vec4<T>::type V4;
@@ -2919,7 +2925,7 @@ static_assert(kWavesPerBlock == 4, "k_trtri_panel combines four partial sums");
 
 // tiles[t] = (subdomain, I << 16 | J) for the output tiles I >= J of every block.
 template <typename T>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock, kMfmaWaves)
 k_gram(const T *__restrict__ X, T *__restrict__ Kinv, const long long *__restrict__ koff,
        const int *__restrict__ ni, const int2 *__restrict__ tiles, int ntiles) {
   const int t = blockIdx.x * kWavesPerBlock + wave_id();
@@ -3084,7 +3090,7 @@ __global__ void k_pack_strips(long long n, const double *__restrict__ val,
 // (column 16 J + c of subdomain k's local interface) has the same bits on
 // every run.  X in the factor's precision, W in FP64.
 template <typename T>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock, kMfmaWaves)
 k_schur_wsq(const T *__restrict__ X, const double *__restrict__ packed,
             const long long *__restrict__ koff, const long long *__restrict__ voff,
             const int *__restrict__ ni, const int *__restrict__ goff, const int4 *__restrict__ items,

@@ -43,8 +43,8 @@ struct Ops {
   void *g_val = nullptr;   // [K_GG | K_GI] values (T)
   double *diag = nullptr;  // diag(S)
   double *dinv = nullptr;  // 1 / diag(S)
-  void *tI_val = nullptr;  // 16x8 units of K_IG (T), wide batches
-  void *tG_val = nullptr;  // 16x8 units of [K_GG | K_GI] (T), wide batches
+  void *tI_val = nullptr;  // units of K_IG (T), wide batches
+  void *tG_val = nullptr;  // units of [K_GG | K_GI] (T), wide batches
   void *kinv_t = nullptr;  // K_II^{-1} packed into 16x16 tiles (T), wide batches
   bool ready = false;
 };
@@ -101,15 +101,15 @@ struct dd_ctx {
   int *d_ig_ptr = nullptr, *d_ig_col = nullptr;
   int *d_g_ptr = nullptr, *d_g_split = nullptr, *d_g_col = nullptr;
   // wide batches on the matrix cores (built when max_nrhs >= 8 and there are
-  // interiors): 16x8 units of K_IG over blocks of kTileRbI x 16 interior rows,
-  // of [K_GG | K_GI] over blocks of kTileRbG x 16 interface rows (entries
-  // [ptr, split) multiply p, [split, ptr+1) multiply w; t_nI, t_nG count 16x8
-  // units), and the (subdomain, 16-row tile) work items of the interior solve
+  // interiors): units of K_IG over blocks of 16 interior rows, of [K_GG | K_GI]
+  // over blocks of 16 interface rows (units [ptr, split) multiply p, [split,
+  // ptr+1) multiply w; t_nI, t_nG count units), and the (subdomain, 16-row
+  // tile) work items of the interior solve
   bool tiles = false;
   int t_nrbI = 0, t_nrbG = 0, n_dit = 0;
   size_t t_nI = 0, t_nG = 0;
-  int *d_tI_ptr = nullptr, *d_tI_col = nullptr;
-  int *d_tG_ptr = nullptr, *d_tG_split = nullptr, *d_tG_col = nullptr;
+  int *d_tI_ptr = nullptr, *d_tG_ptr = nullptr, *d_tG_split = nullptr;
+  int *d_tI_col = nullptr, *d_tG_col = nullptr;   // 16 columns per unit
   double *d_tI_val64 = nullptr, *d_tG_val64 = nullptr;
   int2 *d_dit = nullptr;
   long long t_kpack = 0;              // elements of the packed dense blocks (16x16 tiles)
@@ -296,82 +296,65 @@ dd_status validate(const dd_problem *p) {
   return DD_OK;
 }
 
-// Block CSR of 16x8 units over row blocks of RB x 16 rows and column blocks of
-// kTU = 8 columns.  Row i's entries [ptr[i], mid) (columns in [0, ncol1)) go
-// to the first part of its block, entries [mid, ptr[i+1]) (columns in [0,
-// ncol2)) to the second, mid = split[i] (or ptr[i+1] when split is null).
-// Within a part the column blocks are in increasing order; an entry (row
-// block, column block) holds RB units, one per 16-row slice of the block (zero
-// where the slice has no entry), so that one slice of the multiplied vector
-// serves RB units.  Values are placed in the A-operand order of two steps of
-// the 16x16x4 matrix instructions (UnitLayout in dd_tiles.h), zeros elsewhere.
-// Returns the number of 16x8 units (entries x RB).
+// Units of a sparse matrix (dd_tiles.h): per block of 16 rows the columns its
+// rows use, sixteen to a unit.  Row i's entries [ptr[i], mid) (columns in [0,
+// ncol1)) go to the first part of its block, entries [mid, ptr[i+1]) (columns in
+// [0, ncol2)) to the second, mid = split[i] (or ptr[i+1] when split is null).
+// Within a part the columns are in increasing order; the last unit of a part is
+// filled up with its last column (and zero values).  Returns the number of
+// units; the values are placed on the device (k_fill_units).
 struct TileSet {
   std::vector<int> ptr, split, col;
-  std::vector<double> val;
 };
 constexpr int kTileMinLd = 8;     // narrowest batch served by the tiled products
-// 16-row slices per row block: the interface rows (the largest product) share
-// each vector slice between two slices of rows; the interior rows K_IG, with
-// fewer row blocks, keep one (their launch would otherwise fill the chip
-// only half).
-constexpr int kTileRbG = 2, kTileRbI = 1;
 
-size_t build_tiles(int nrows, const int *ptr, const int *split, const int *col, const double *val,
-                   int ncol1, int ncol2, int RB, TileSet *ts) {
-  const int H = RB * kT;
-  const int nrb = (nrows + H - 1) / H;
-  std::vector<int> slot1((ncol1 + kTU - 1) / kTU + 1, -1), slot2((ncol2 + kTU - 1) / kTU + 1, -1);
-  std::vector<int> cb1, cb2;
-  size_t nent = 0;
-  if (ts) {
-    ts->ptr.assign(nrb + 1, 0);
-    ts->split.assign(nrb, 0);
-    ts->col.clear();
-    ts->val.clear();
-  }
-  for (int rb = 0; rb < nrb; ++rb) {
-    const int i0 = rb * H, i1 = std::min(nrows, i0 + H);
-    cb1.clear();
-    cb2.clear();
-    for (int i = i0; i < i1; ++i) {
-      const int mid = split ? split[i] : ptr[i + 1];
-      for (int a = ptr[i]; a < mid; ++a) {
-        const int cb = col[a] / kTU;
-        if (slot1[cb] < 0) { slot1[cb] = 0; cb1.push_back(cb); }
-      }
-      for (int a = mid; a < ptr[i + 1]; ++a) {
-        const int cb = col[a] / kTU;
-        if (slot2[cb] < 0) { slot2[cb] = 0; cb2.push_back(cb); }
-      }
-    }
-    std::sort(cb1.begin(), cb1.end());
-    std::sort(cb2.begin(), cb2.end());
-    const size_t base = nent;
-    for (size_t t = 0; t < cb1.size(); ++t) slot1[cb1[t]] = (int)(base + t);
-    for (size_t t = 0; t < cb2.size(); ++t) slot2[cb2[t]] = (int)(base + cb1.size() + t);
-    nent += cb1.size() + cb2.size();
-    if (ts) {
-      for (int cb : cb1) ts->col.push_back(cb);
-      ts->split[rb] = (int)ts->col.size();
-      for (int cb : cb2) ts->col.push_back(cb);
-      ts->ptr[rb + 1] = (int)ts->col.size();
-      ts->val.resize(nent * RB * kUV, 0.0);
+size_t build_tiles(int nrows, const int *ptr, const int *split, const int *col, int ncol1, int ncol2,
+                   TileSet *ts) {
+  const int nrb = (nrows + kT - 1) / kT;
+  // columns of a part in increasing order: marked in a bit map, read back word by word
+  std::vector<uint64_t> map((std::max(ncol1, ncol2) + 63) / 64 + 1, 0);
+  std::vector<int> cols, count(2 * (size_t)nrb, 0);     // columns of every part, one after the other
+  size_t nunit = 0;
+  for (int rb = 0; rb < nrb; ++rb)
+    for (int part = 0; part < 2; ++part) {
+      const int i0 = rb * kT, i1 = std::min(nrows, i0 + kT);
+      size_t lo = map.size(), hi = 0;
       for (int i = i0; i < i1; ++i) {
         const int mid = split ? split[i] : ptr[i + 1];
-        const int h = (i - i0) / kT, ii = (i - i0) % kT;
-        for (int a = ptr[i]; a < ptr[i + 1]; ++a) {
-          const int t = a < mid ? slot1[col[a] / kTU] : slot2[col[a] / kTU];
-          const int kk = col[a] % kTU;
-          // U[ii][kk] of slice h is held by lane (kk % 4) * 16 + ii at step kk / 4
-          ts->val[((size_t)t * RB + h) * kUV + UnitLayout::pos((kk % 4) * kT + ii, kk / 4)] += val[a];
+        for (int a = part ? mid : ptr[i], e = part ? ptr[i + 1] : mid; a < e; ++a) {
+          const size_t w = (size_t)col[a] / 64;
+          map[w] |= 1ull << (col[a] % 64);
+          lo = std::min(lo, w);
+          hi = std::max(hi, w + 1);
         }
       }
+      int n = 0;
+      for (size_t w = lo; w < hi; ++w) {
+        uint64_t m = map[w];
+        map[w] = 0;
+        n += __builtin_popcountll(m);
+        for (; ts && m; m &= m - 1) cols.push_back((int)(w * 64) + __builtin_ctzll(m));
+      }
+      count[2 * (size_t)rb + part] = n;
+      nunit += (n + kT - 1) / kT;
     }
-    for (int cb : cb1) slot1[cb] = -1;
-    for (int cb : cb2) slot2[cb] = -1;
+  if (!ts) return nunit;
+  ts->ptr.assign(nrb + 1, 0);
+  ts->split.assign(nrb, 0);
+  ts->col.resize(nunit * kT);
+  const int *c = cols.data();
+  size_t u = 0;
+  for (int rb = 0; rb < nrb; ++rb) {
+    for (int part = 0; part < 2; ++part) {
+      const int n = count[2 * (size_t)rb + part], nu = (n + kT - 1) / kT;
+      if (part) ts->split[rb] = (int)u;
+      for (int t = 0; t < nu * kT; ++t) ts->col[u * kT + unit_slot(t)] = c[std::min(t, n - 1)];
+      c += n;
+      u += nu;
+    }
+    ts->ptr[rb + 1] = (int)u;
   }
-  return nent * RB;
+  return nunit;
 }
 
 // Tiles of a problem (interior rows x interface columns, interface rows x
@@ -394,7 +377,7 @@ void count_problem_tiles(const dd_problem *p, size_t *nI, size_t *nG) {
       iptr.push_back((int)icol.size());
     }
   }
-  *nI = build_tiles(NI, iptr.data(), nullptr, icol.data(), nullptr, p->n_gamma, 1, kTileRbI, nullptr);
+  *nI = build_tiles(NI, iptr.data(), nullptr, icol.data(), p->n_gamma, 1, nullptr);
   std::vector<int> gptr(1, 0), gsplit, gcol;
   for (int j = 0; j < p->n_gamma; ++j) {
     for (int a = p->kgg_rowptr[j]; a < p->kgg_rowptr[j + 1]; ++a) gcol.push_back(p->kgg_col[a]);
@@ -402,8 +385,8 @@ void count_problem_tiles(const dd_problem *p, size_t *nI, size_t *nG) {
     for (int v : gi[j]) gcol.push_back(v);
     gptr.push_back((int)gcol.size());
   }
-  *nG = build_tiles(p->n_gamma, gptr.data(), gsplit.data(), gcol.data(), nullptr, p->n_gamma,
-                    std::max(1, NI), kTileRbG, nullptr);
+  *nG = build_tiles(p->n_gamma, gptr.data(), gsplit.data(), gcol.data(), p->n_gamma,
+                    std::max(1, NI), nullptr);
 }
 
 size_t footprint_bytes(const dd_problem *p, dd_precision prec, int max_nrhs) {
@@ -428,9 +411,8 @@ size_t footprint_bytes(const dd_problem *p, dd_precision prec, int max_nrhs) {
   if (max_nrhs >= kTileMinLd && p->n_sub > 0 && p->n_gamma > 0) {    // tiles of the wide batches
     size_t tI = 0, tG = 0;
     count_problem_tiles(p, &tI, &tG);
-    const size_t nrbI = (NI + kT * kTileRbI - 1) / (kT * kTileRbI),
-                 nrbG = (p->n_gamma + kT * kTileRbG - 1) / (kT * kTileRbG);
-    b += (tI + tG) * (4 + kUV * 8) + (nrbI + 1) * 4 + (2 * nrbG + 1) * 4 + NI * 8 / kT + 64;
+    const size_t nrbI = (NI + kT - 1) / kT, nrbG = (p->n_gamma + kT - 1) / kT;
+    b += (tI + tG) * (kT * 4 + kUV * 8) + (nrbI + 1) * 4 + (2 * nrbG + 1) * 4 + NI * 8 / kT + 64;
     if (prec == DD_MIXED) b += (tI + tG) * kUV * 4;
     size_t kp = 0;                       // packed K_II (FP64) and K_II^{-1} (T)
     for (int k = 0; k < p->n_sub; ++k) {
@@ -705,27 +687,20 @@ void launch_tile_rows_t(dd_ctx *c, bool interface_rows, const VT *val, const dou
   const int nrb = interface_rows ? c->t_nrbG : c->t_nrbI;
   const int nrows = interface_rows ? c->n_gamma : c->NI;
   if (nrb <= 0) return;
-  const dim3 g(nrb), b(kTW * kWave);
   const int *ptr = interface_rows ? c->d_tG_ptr : c->d_tI_ptr;
   const int *split = interface_rows ? c->d_tG_split : nullptr;
-  const int *col = interface_rows ? c->d_tG_col : c->d_tI_col;
-  const int n2 = interface_rows ? c->NI : 0;
-  if (DOT) c->gamma_parts = (int)((g.x + kPGroup - 1) / kPGroup);   // group sums of p^T q
+  const int4 *col = (const int4 *)(interface_rows ? c->d_tG_col : c->d_tI_col);
+  if (DOT) c->gamma_parts = (nrb + kPGroup - 1) / kPGroup;          // group sums of p^T q
   hipEvent_t e0 = nullptr, e1 = nullptr;
-  auto launch = [&](auto kern) {
-    if (DOT && kernel_events(c, DD_PHASE_GAMMA, &e0, &e1))
-      hipExtLaunchKernelGGL(kern, g, b, 0, c->stream, e0, e1, 0, nrb, nrows, ptr, split, col, val, x1,
-                            c->n_gamma, x2, n2, ld, base, c1, c2, out, c->red, run, x1f, x2f);
-    else
-      hipLaunchKernelGGL(kern, g, b, 0, c->stream, nrb, nrows, ptr, split, col, val, x1, c->n_gamma, x2, n2,
-                         ld, base, c1, c2, out, c->red, run, x1f, x2f);
-  };
-  // two entries' operands in flight per wave: three or four measured slower on
-  // the peridynamic 32-column batch (FP64 interface launch 78 -> 81 us with
-  // three; FP32 57 us with two or three, 59 with four)
-  constexpr int kDepth = 2;
-  if (interface_rows) launch(k_tile_rows<VT, NCB, DOT, kDepth, kTileRbG>);
-  else launch(k_tile_rows<VT, NCB, DOT, kDepth, kTileRbI>);
+  constexpr int kDepth = 2, kWaves = 4;        // units in flight per wave, waves per row block
+  constexpr auto kern = k_tile_rows<VT, NCB, DOT, kDepth, kWaves>;
+  const dim3 g(nrb), b(kWaves * kWave);
+  if (DOT && kernel_events(c, DD_PHASE_GAMMA, &e0, &e1))
+    hipExtLaunchKernelGGL(kern, g, b, 0, c->stream, e0, e1, 0, nrb, nrows, ptr, split, col, val, x1, x2, ld, base,
+                          c1, c2, out, c->red, run, x1f, x2f);
+  else
+    hipLaunchKernelGGL(kern, g, b, 0, c->stream, nrb, nrows, ptr, split, col, val, x1, x2, ld, base, c1, c2, out,
+                       c->red, run, x1f, x2f);
 }
 
 // out = base + c1 * (tiled K_IG or K_GG) x1 + c2 * (tiled K_GI) x2 with the
@@ -990,10 +965,10 @@ dd_status factor_impl(dd_ctx *c, int pi) {
     hipLaunchKernelGGL(k_to_f32, dim3(1024), dim3(256), 0, c->stream, c->nnz_g, c->d_g_val64,
                        (float *)o.g_val);
     if (c->tiles) {
-      hipLaunchKernelGGL(k_units_to_f32, dim3(1024), dim3(256), 0, c->stream, c->t_nI / kTileRbI, kTileRbI,
-                         c->d_tI_val64, (float *)o.tI_val);
-      hipLaunchKernelGGL(k_units_to_f32, dim3(1024), dim3(256), 0, c->stream, c->t_nG / kTileRbG, kTileRbG,
-                         c->d_tG_val64, (float *)o.tG_val);
+      hipLaunchKernelGGL(k_units_to_f32, dim3(1024), dim3(256), 0, c->stream, c->t_nI, c->d_tI_val64,
+                         (float *)o.tI_val);
+      hipLaunchKernelGGL(k_units_to_f32, dim3(1024), dim3(256), 0, c->stream, c->t_nG, c->d_tG_val64,
+                         (float *)o.tG_val);
     }
     HIPCHK(c, hipGetLastError());
   }
@@ -1851,11 +1826,11 @@ dd_status dd_setup(const dd_problem *p, void *hip_stream, int32_t max_nrhs, dd_c
   // tiles of the wide-batch products (matrix cores)
   if (c->ldmax >= kTileMinLd && c->n_sub > 0 && c->n_gamma > 0 && !getenv("DD_NO_TILES")) {
     TileSet ti, tg;
-    c->t_nI = build_tiles(NI, igptr.data(), nullptr, igcol.data(), igval.data(), c->n_gamma, 1, kTileRbI, &ti);
-    c->t_nG = build_tiles(c->n_gamma, gptr.data(), gsplit.data(), gcol.data(), gval.data(), c->n_gamma,
-                          std::max(1, NI), kTileRbG, &tg);
-    c->t_nrbI = (NI + kT * kTileRbI - 1) / (kT * kTileRbI);
-    c->t_nrbG = (c->n_gamma + kT * kTileRbG - 1) / (kT * kTileRbG);
+    c->t_nI = build_tiles(NI, igptr.data(), nullptr, igcol.data(), c->n_gamma, 1, &ti);
+    c->t_nG = build_tiles(c->n_gamma, gptr.data(), gsplit.data(), gcol.data(), c->n_gamma,
+                          std::max(1, NI), &tg);
+    c->t_nrbI = (NI + kT - 1) / kT;
+    c->t_nrbG = (c->n_gamma + kT - 1) / kT;
     // Interior-solve work items (subdomain, 16-row tile).  Workgroup b runs on
     // XCD b % 8: every subdomain's items go to one XCD (its slices of y are then
     // cached in one L2), subdomains by decreasing work to the least loaded XCD,
@@ -1881,17 +1856,25 @@ dd_status dd_setup(const dd_problem *p, void *hip_stream, int32_t max_nrhs, dd_c
       for (int x = 0; x < kXcd; ++x) items.push_back(i < bins[x].size() ? bins[x][i] : make_int2(-1, 0));
     c->n_dit = (int)items.size();
     for (TileSet *t : {&ti, &tg})          // uploads need at least one element
-      if (t->col.empty()) {
-        t->col.push_back(0);
-        t->val.assign((size_t)kTileRbG * kUV, 0.0);
-      }
+      if (t->col.empty()) t->col.assign(kT, 0);
     if ((s = upload(c, &c->d_tI_ptr, ti.ptr.data(), ti.ptr.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_tI_col, ti.col.data(), ti.col.size())) != DD_OK) return bail(s);
-    if ((s = upload(c, &c->d_tI_val64, ti.val.data(), ti.val.size())) != DD_OK) return bail(s);
+    if ((s = dalloc(c, &c->d_tI_val64, std::max<size_t>(1, c->t_nI) * kUV)) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_tG_ptr, tg.ptr.data(), tg.ptr.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_tG_split, tg.split.data(), tg.split.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_tG_col, tg.col.data(), tg.col.size())) != DD_OK) return bail(s);
-    if ((s = upload(c, &c->d_tG_val64, tg.val.data(), tg.val.size())) != DD_OK) return bail(s);
+    if ((s = dalloc(c, &c->d_tG_val64, std::max<size_t>(1, c->t_nG) * kUV)) != DD_OK) return bail(s);
+    if (hipMemsetAsync(c->d_tI_val64, 0, std::max<size_t>(1, c->t_nI) * kUV * sizeof(double), c->stream) != hipSuccess ||
+        hipMemsetAsync(c->d_tG_val64, 0, std::max<size_t>(1, c->t_nG) * kUV * sizeof(double), c->stream) != hipSuccess) {
+      c->err = "hipMemset failed";
+      return bail(DD_EHIP);
+    }
+    hipLaunchKernelGGL(k_fill_units, dim3(grid_for(NI, kWave)), dim3(kWave), 0, c->stream, NI, c->d_ig_ptr,
+                       (const int *)nullptr, c->d_ig_col, c->d_ig_val64, c->d_tI_ptr, (const int *)nullptr,
+                       c->d_tI_col, c->d_tI_val64);
+    hipLaunchKernelGGL(k_fill_units, dim3(grid_for(c->n_gamma, kWave)), dim3(kWave), 0, c->stream, c->n_gamma,
+                       c->d_g_ptr, c->d_g_split, c->d_g_col, c->d_g_val64, c->d_tG_ptr, c->d_tG_split, c->d_tG_col,
+                       c->d_tG_val64);
     if ((s = upload(c, &c->d_dit, items.data(), items.size())) != DD_OK) return bail(s);
     std::vector<long long> toff(c->n_sub + 1, 0);
     for (int k = 0; k < c->n_sub; ++k) {

@@ -3,15 +3,18 @@
 // With 8 or more right-hand sides the CSR row products of the CG iteration are
 // bound by their vector gathers: every nonzero fetches a whole ld-wide slice
 // of the vector it multiplies, so at 32 columns the gathers move about 30
-// times the bytes of the matrix.  Here the coupling matrices are stored as
-// dense units of 16 rows x 8 columns (block CSR over blocks of 16 or 32 rows
-// and 8 columns: two k-steps of the 16x16x4 matrix instructions) and every
-// unit is applied to an 8-row slice of the multiplied vector by
-// v_mfma_f64_16x16x4f64: a slice is then fetched once per unit instead of
-// once per nonzero, and the matrix bytes stream once per iteration.  (Units 8
-// columns wide leave fewer stored zeros than 16x16 tiles on nonlocal
-// operators: on the peridynamic interface rows 54 % of the values are
-// nonzero against 47 %.)
+// times the bytes of the matrix.  Here the coupling matrices are stored by
+// blocks of 16 rows: the columns that any row of a block uses, sixteen at a
+// time, as dense units of 16 rows x 16 listed columns (four k-steps of the
+// 16x16x4 matrix instructions).  A row of the multiplied vector is one
+// contiguous ld-wide segment wherever it lies, and the instruction's four
+// column slots are loaded by different lanes, so the listed columns need not
+// be neighbours: a unit's vector rows are gathered at no extra cost, each
+// fetched once per block instead of once per nonzero.  Naming single columns
+// instead of blocks of them leaves fewer stored zeros: on the peridynamic
+// interface rows (h = 1/160) 73 % of the values are nonzero, against 62 % with
+// aligned blocks of 8 columns, 54 % with 16, and 63 % with single columns over
+// 32-row blocks.
 //
 // The interior solves w = K_II^-1 y, a dense product per subdomain, use the
 // same instruction on 16x16 tiles of the explicit inverse (FP64), or
@@ -52,47 +55,50 @@ template <> struct TileLayout<float> {
   static __host__ __device__ constexpr int step(int p) { return p & 3; }
 };
 
-// Coupling units: 16 rows x kTU = 8 columns, kUV = 128 values; lane l holds
-// U[l % 16][4 s + l / 16], the A operand of step s (s = 0, 1), at 2 l + s (one
-// 16-byte load per lane in FP64).
-constexpr int kTU = 8, kUV = kT * kTU;
-struct UnitLayout {
-  static __host__ __device__ constexpr int pos(int l, int s) { return 2 * l + s; }
-};
+// Coupling units: 16 rows x 16 listed columns in the tile order above; unit t
+// lists its columns at tcol[t].[g], the four of lane group g = lane / 16 (its
+// A operands' columns in step order), as one int4.
+constexpr int kUV = kT * kT;
+// Place in a block's column lists of its t-th column (in increasing order):
+// column kk = t % 16 of unit t / 16 is step kk / 4 of lane group kk % 4.
+__host__ __device__ constexpr int unit_slot(int t) { return t / kT * kT + t % 4 * 4 + t % kT / 4; }
 
-// A operand of a streamed FP64 coupling unit (nontemporal loads).
-__device__ __forceinline__ void unit_a(const double *unit, int lane, double (&a)[2]) {
-  typedef double v2 __attribute__((ext_vector_type(2)));
-  const v2 u = __builtin_nontemporal_load((const v2 *)(unit + 2 * lane));
-  a[0] = u[0];
-  a[1] = u[1];
-}
-
-// FP32 copies (mixed path) interleave the RB units of an entry per lane --
-// lane l holds slice h, step s at RB (2 l) + 2 h + s -- so that a lane loads
-// its operands of a two-slice entry with one 16-byte load, as the FP64 units
-// do per slice.
-template <int RB>
-__device__ __forceinline__ void entry_a32(const float *entry, int lane, float (&a)[RB][2]) {
-  typedef float vt __attribute__((ext_vector_type(2 * RB)));
-  const vt u = __builtin_nontemporal_load((const vt *)(entry + 2 * RB * lane));
-#pragma unroll
-  for (int h = 0; h < RB; ++h) {
-    a[h][0] = u[2 * h];
-    a[h][1] = u[2 * h + 1];
+// Values of a CSR matrix into its (zeroed) FP64 units: one thread per row, which
+// finds each entry's column in its block's list (units [tptr, tsplit) hold
+// the entries [ptr, split), units [tsplit, tptr + 1) the others; split and tsplit
+// may be nullptr) and adds the entries in order.
+__global__ void __launch_bounds__(kWave)
+k_fill_units(int nrows, const int *__restrict__ ptr, const int *__restrict__ split, const int *__restrict__ col,
+             const double *__restrict__ val, const int *__restrict__ tptr, const int *__restrict__ tsplit,
+             const int *__restrict__ tcol, double *__restrict__ unit) {
+  const int i = blockIdx.x * kWave + threadIdx.x;
+  if (i >= nrows) return;
+  const int rb = i / kT, ii = i % kT;
+  const int t0 = tptr[rb], t2 = tptr[rb + 1], t1 = tsplit ? tsplit[rb] : t2;
+  const int e = ptr[i + 1], mid = split ? split[i] : e;
+  for (int a = ptr[i]; a < e; ++a) {
+    const int u0 = a < mid ? t0 : t1, u1 = a < mid ? t1 : t2, c = col[a];
+    const int *list = tcol + (size_t)u0 * kT;
+    int lo = 0, hi = (u1 - u0) * kT - 1;          // first place of c
+    while (lo < hi) {
+      const int m = (lo + hi) / 2;
+      if (list[unit_slot(m)] < c) lo = m + 1;
+      else hi = m;
+    }
+    const int kk = lo % kT;
+    // U[ii][kk] is held by lane (kk % 4) * 16 + ii at step kk / 4
+    unit[((size_t)u0 + lo / kT) * kUV + TileLayout<double>::pos((kk % 4) * kT + ii, kk / 4)] += val[a];
   }
 }
 
-// FP64 units (entries of RB units, UnitLayout each) -> the interleaved FP32
-// copies read by entry_a32.
-__global__ void k_units_to_f32(size_t nent, int RB, const double *__restrict__ in, float *__restrict__ out) {
-  const size_t per = (size_t)RB * kUV;
-  for (size_t o = (size_t)blockIdx.x * blockDim.x + threadIdx.x; o < nent * per;
+// FP64 tiles -> the FP32 copies of the mixed path (the same values rounded, in
+// the FP32 tile order).
+__global__ void k_units_to_f32(size_t nunit, const double *__restrict__ in, float *__restrict__ out) {
+  for (size_t o = (size_t)blockIdx.x * blockDim.x + threadIdx.x; o < nunit * kUV;
        o += (size_t)gridDim.x * blockDim.x) {
-    const size_t t = o / per;
-    const int r = (int)(o - t * per);
-    const int l = r / (2 * RB), h = (r >> 1) % RB, st = r & 1;
-    out[o] = (float)in[(t * RB + h) * kUV + UnitLayout::pos(l, st)];
+    const size_t t = o / kUV;
+    const int r = (int)(o - t * kUV);
+    out[o] = (float)in[t * kUV + TileLayout<double>::pos(TileLayout<float>::lane(r), TileLayout<float>::step(r))];
   }
 }
 
@@ -130,155 +136,111 @@ __device__ __forceinline__ void slice_row(const float *__restrict__ p, float (&v
   }
 }
 
-// One 8-row slice of x (rows cb*8 .. cb*8+7, DD layout with leading
-// dimension ld) in the B-operand order: lane l takes row cb*8 + 4 s + l/16 for
-// step s, its columns as above.  Rows past the last row n - 1 read row n - 1
-// (the unit entries they meet are zero).  The loads are unconditional, so the
-// compiler can count them when it waits for a buffer.
-template <int NCB>
-__device__ __forceinline__ void load_slice(const double *__restrict__ x, int n, int ld, int cb,
-                                           double (&xv)[2][NCB]) {
-  const int lane = lane_id(), g = lane >> 4, l16 = lane & 15;
-  const double *p = x + slice_col0<NCB>(l16, ld);
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const int row = min(cb * kTU + 4 * s + g, n - 1);
-    slice_row<NCB>(p + (size_t)row * ld, xv[s]);
-  }
+// A operand of a streamed coupling unit, FP64 or FP32 (nontemporal loads).
+__device__ __forceinline__ void unit_a(const double *unit, int lane, double (&a)[4]) {
+  typedef double v2 __attribute__((ext_vector_type(2)));
+  const v2 u = __builtin_nontemporal_load((const v2 *)(unit + 2 * lane));
+  const v2 v = __builtin_nontemporal_load((const v2 *)(unit + 128 + 2 * lane));
+  a[0] = u[0]; a[1] = u[1]; a[2] = v[0]; a[3] = v[1];
 }
-// (FP32 copy of the vector: the same slices, half the bytes)
-template <int NCB>
-__device__ __forceinline__ void load_slice(const float *__restrict__ x, int n, int ld, int cb,
-                                           float (&xv)[2][NCB]) {
-  const int lane = lane_id(), g = lane >> 4, l16 = lane & 15;
-  const float *p = x + slice_col0<NCB>(l16, ld);
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const int row = min(cb * kTU + 4 * s + g, n - 1);
-    slice_row<NCB>(p + (size_t)row * ld, xv[s]);
-  }
+__device__ __forceinline__ void unit_a(const float *unit, int lane, float (&a)[4]) {
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  const v4 v = __builtin_nontemporal_load((const v4 *)(unit + 4 * lane));
+  a[0] = v[0]; a[1] = v[1]; a[2] = v[2]; a[3] = v[3];
 }
 
-// acc[h][q] += U_h * X over the entries t0, t0 + st, t0 + 2 st, ... (< t1) of
-// one row block, in that order (t0, t1, st uniform over the wave); entry t holds
-// the RB units U_h (16-row slice h of the block) at tval + (t RB + h) kUV, all
-// multiplying the same 8-row slice of x, which is loaded once.  The entries'
-// column blocks are fetched 64 at a time, one per lane, and broadcast by
-// readlane; D register buffers hold the operands of the next D entries while an
-// entry's instructions run (the last loads of a wave repeat its last entry and
-// are not used).  Scheduling barriers keep every group of loads in program
+// acc[q] += sgn * U * X over the units t0, t0 + st, t0 + 2 st, ... (< t1) of one
+// row block, in that order (t0, t1, st uniform over the wave).  FP64 units run
+// on v_mfma_f64_16x16x4f64.  FP32 units (mixed path) run on
+// v_mfma_f32_16x16x4f32 (twice the rate): the vector is rounded to FP32, two
+// steps accumulate 8 products per output element in FP32, and these sums are
+// added to the FP64 accumulators, so FP32 rounding enters only within them
+// (rows are then in the FP32 instruction's order: row 4 (l / 16) + r of lane l,
+// register r).  A pass of the loop runs unit j while the
+// operands of units j + 1 .. j + D - 1 and the column lists of the D after them
+// are in flight.  Scheduling barriers keep every group of loads in program
 // order, so that the instructions of one buffer wait only for that buffer's
-// loads, the other buffers' staying in flight.
-template <int NCB, int D, int RB>
-__device__ __forceinline__ void tile_row_acc(int t0, int t1, int st, const int *__restrict__ tcol,
-                                             const double *__restrict__ tval, const double *__restrict__ x,
-                                             int n, int ld, double sgn, dbl4 (&acc)[RB][NCB]) {
+// loads; the loads past a wave's last unit are skipped.
+template <int NCB, int D, typename VT, typename XT>
+__device__ __forceinline__ void tile_row_acc(int t0, int t1, int st, const int4 *__restrict__ tcol,
+                                             const VT *__restrict__ tval, const XT *__restrict__ x, int ld,
+                                             double sgn, dbl4 (&acc)[NCB]) {
   const int cnt = t0 < t1 ? (t1 - t0 + st - 1) / st : 0;
-  const int lane = lane_id();
-  for (int base = 0; base < cnt; base += kWave) {
-    const int nb = min(kWave, cnt - base);
-    const int mycol = lane < nb ? tcol[t0 + (base + lane) * st] : 0;
-    const double *tv = tval + (size_t)(t0 + base * st) * RB * kUV;
-    const size_t tstride = (size_t)st * RB * kUV;
-    double a[D][RB][2], xs[D][2][NCB];
+  if (cnt == 0) return;
+  const int lane = lane_id(), g = lane >> 4;
+  const XT *xc = x + slice_col0<NCB>(lane & 15, ld);
+  const int4 *cl = tcol + (size_t)t0 * 4 + g;
+  const VT *tv = tval + (size_t)t0 * kUV;
+  VT a[D][4];
+  XT xs[D][4][NCB];
+  int4 ix[D];
+  auto list = [&](int d, int j) { ix[d] = cl[(size_t)j * st * 4]; };
+  auto load = [&](int d, int j) {
+    unit_a(tv + (size_t)j * st * kUV, lane, a[d]);
+    slice_row<NCB>(xc + (size_t)ix[d].x * ld, xs[d][0]);
+    slice_row<NCB>(xc + (size_t)ix[d].y * ld, xs[d][1]);
+    slice_row<NCB>(xc + (size_t)ix[d].z * ld, xs[d][2]);
+    slice_row<NCB>(xc + (size_t)ix[d].w * ld, xs[d][3]);
+  };
+  auto mma = [&](int d) {
+    if constexpr (std::is_same<VT, float>::value) {
+      const float fs = (float)sgn;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        flt4 c[NCB];
+#pragma unroll
+        for (int q = 0; q < NCB; ++q) {
+          const flt4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+          c[q] = mfma16x16x4(a[d][2 * h], fs * (float)xs[d][2 * h][q], zero);
+          c[q] = mfma16x16x4(a[d][2 * h + 1], fs * (float)xs[d][2 * h + 1][q], c[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < NCB; ++q)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[q][r] += (double)c[q][r];
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int q = 0; q < NCB; ++q) acc[q] = mfma16x16x4((double)a[d][s], sgn * (double)xs[d][s][q], acc[q]);
+    }
+  };
+  // (list and operand buffers are filled past the end with the last unit's)
+#pragma unroll
+  for (int d = 0; d < D; ++d) list(d, min(d, cnt - 1));
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    load(d, min(d, cnt - 1));
+    list(d, min(d + D, cnt - 1));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  int j = 0;
+  for (; j + 2 * D <= cnt; j += D) {
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      const int jd = min(d, nb - 1);
-#pragma unroll
-      for (int h = 0; h < RB; ++h) unit_a(tv + jd * tstride + h * kUV, lane, a[d][h]);
-      load_slice<NCB>(x, n, ld, __builtin_amdgcn_readlane(mycol, jd), xs[d]);
+      mma(d);
+      __builtin_amdgcn_sched_barrier(0);
+      load(d, j + d + D);
+      list(d, min(j + d + 2 * D, cnt - 1));
       __builtin_amdgcn_sched_barrier(0);
     }
-    for (int j = 0; j < nb; j += D) {
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        if (j + d < nb) {
-#pragma unroll
-          for (int s = 0; s < 2; ++s)              // sgn = +-1: exact
-#pragma unroll
-            for (int q = 0; q < NCB; ++q) xs[d][s][q] *= sgn;
-#pragma unroll
-          for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int h = 0; h < RB; ++h)
-#pragma unroll
-              for (int q = 0; q < NCB; ++q) acc[h][q] = mfma16x16x4(a[d][h][s], xs[d][s][q], acc[h][q]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        const int jn = min(j + d + D, nb - 1);
-#pragma unroll
-        for (int h = 0; h < RB; ++h) unit_a(tv + jn * tstride + h * kUV, lane, a[d][h]);
-        load_slice<NCB>(x, n, ld, __builtin_amdgcn_readlane(mycol, jn), xs[d]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
   }
+  // at most 2 D - 1 units are left, the first D of them loaded
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    if (j + d < cnt) mma(d);
+    __builtin_amdgcn_sched_barrier(0);
+    if (j + d + D < cnt) load(d, j + d + D);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (j + d + D < cnt) mma(d);
 }
 
-// tile_row_acc for FP32 units (mixed path, entries interleaved as read by
-// entry_a32) on v_mfma_f32_16x16x4f32: the slice is rounded to FP32, the two
-// steps of an entry accumulate its 8 products per output element in FP32, and
-// each entry's sums are added to the FP64 accumulators, so FP32 rounding
-// enters only within one entry.  The accumulators hold rows in the FP32
-// instruction's order (row 4 (l / 16) + r of lane l, register r).
-template <int NCB, int D, int RB, typename XT>
-__device__ __forceinline__ void tile_row_acc_f32(int t0, int t1, int st, const int *__restrict__ tcol,
-                                                 const float *__restrict__ tval, const XT *__restrict__ x,
-                                                 int n, int ld, double sgn, dbl4 (&acc)[RB][NCB]) {
-  const int cnt = t0 < t1 ? (t1 - t0 + st - 1) / st : 0;
-  const int lane = lane_id();
-  const float fs = (float)sgn;
-  for (int base = 0; base < cnt; base += kWave) {
-    const int nb = min(kWave, cnt - base);
-    const int mycol = lane < nb ? tcol[t0 + (base + lane) * st] : 0;
-    const float *tv = tval + (size_t)(t0 + base * st) * RB * kUV;
-    const size_t tstride = (size_t)st * RB * kUV;
-    float a[D][RB][2];
-    XT xs[D][2][NCB];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const int jd = min(d, nb - 1);
-      entry_a32<RB>(tv + jd * tstride, lane, a[d]);
-      load_slice<NCB>(x, n, ld, __builtin_amdgcn_readlane(mycol, jd), xs[d]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    for (int j = 0; j < nb; j += D) {
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        if (j + d < nb) {
-          flt4 c32[RB][NCB];
-#pragma unroll
-          for (int h = 0; h < RB; ++h)
-#pragma unroll
-            for (int q = 0; q < NCB; ++q)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) c32[h][q][r] = 0.0f;
-#pragma unroll
-          for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int q = 0; q < NCB; ++q) {
-              const float xf = fs * (float)xs[d][s][q];        // sgn = +-1: exact
-#pragma unroll
-              for (int h = 0; h < RB; ++h) c32[h][q] = mfma16x16x4(a[d][h][s], xf, c32[h][q]);
-            }
-#pragma unroll
-          for (int h = 0; h < RB; ++h)
-#pragma unroll
-            for (int q = 0; q < NCB; ++q)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) acc[h][q][r] += (double)c32[h][q][r];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        const int jn = min(j + d + D, nb - 1);
-        entry_a32<RB>(tv + jn * tstride, lane, a[d]);
-        load_slice<NCB>(x, n, ld, __builtin_amdgcn_readlane(mycol, jn), xs[d]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
-}
-
-// Row of a 16-row slice held in accumulator register r of lane group g: the
+// Row of a 16-row block held in accumulator register r of lane group g: the
 // FP64 instruction's order (g + 4 r) or the FP32 one's (4 g + r).
 template <typename VT>
 __device__ __forceinline__ int acc_row(int g, int r) {
@@ -300,100 +262,98 @@ __device__ __forceinline__ int wave_uniform() {
   return __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
 }
 
-// Waves per 16-row block: the block's tiles are dealt to them in turn and their
-// partial products summed in wave order through LDS.
+// Waves per workgroup of the interior solves: a row block's tiles are dealt to
+// them in turn and their partial products summed in wave order through LDS.
 constexpr int kTW = 4;
 
-// One workgroup per block of 16 rows of a tiled matrix:
-//   out = base + sum over waves w of (c1 * (entries [ptr, split) of wave w applied to x1)
-//                                     + c2 * (entries [split, ptr+1) of wave w applied to x2))
-// (split == nullptr: one part, entries [ptr, ptr+1) applied to x1; base may be
-// nullptr; a part whose coefficient is 0 is skipped) for the RB x 16 rows of
-// one row block.  x1 has n1 rows, x2 n2 rows, out nrows rows; all three DD
-// layout with leading dimension ld.  Wave w takes entries b + w, b + w + kTW,
-// ...; the wave sums are added in wave order.  With DOT the workgroup also
+// One workgroup (TW waves) per block of 16 rows of a tiled matrix:
+//   out = base + sum over waves w of (c1 * (units [ptr, split) of wave w applied to x1)
+//                                     + c2 * (units [split, ptr+1) of wave w applied to x2))
+// (split == nullptr: one part, units [ptr, ptr+1) applied to x1; base may be
+// nullptr; a part whose coefficient is 0 is skipped).  All vectors DD layout
+// with leading dimension ld, out nrows rows.  Wave w takes units b + w, b + w +
+// TW, ...; the wave sums are added in wave order.  With DOT the workgroup also
 // writes x1^T out over its rows (rows in order) per column to red.part2, and
 // the last of every kPGroup consecutive workgroups the group sum to red.part3,
 // which the update kernel reduces (the step length of the CG iteration, from
-// p^T S p).  run (may be nullptr): the CG loop's flag of columns still
+// p^T S p).
+// Bound (interface rows, 2 320 blocks of 45 units, 32 columns, h = 1/160):
+// without the unit and vector loads, matrix instructions and the fixed work of a
+// block (column lists, wave sums, dot product) take 50 of the 66 us in FP64,
+// 14 us of it fixed; the units are 215 MB.  32-row blocks of aligned 8-column
+// units took 78.6 us (FP64) and 56 us (FP32, now 47).  Waves per block (2, 4, 8)
+// and units in flight (1 to 4) change it by less than 5 % around 4 and 2.
+// run (may be nullptr): the CG loop's flag of columns still
 // iterating; when it reads 0 the launch does nothing (the loop's host runs a
 // few iterations ahead of the device).  x1f, x2f (FP32 units only; may be
-// nullptr): FP32 copies of x1, x2 whose slices the products load instead.
-template <typename VT, int NCB, bool DOT, int D, int RB>
-__global__ void __launch_bounds__(kTW * kWave)
+// nullptr): FP32 copies of x1, x2 whose rows the products load instead.
+template <typename VT, int NCB, bool DOT, int D, int TW>
+__global__ void __launch_bounds__(TW * kWave, kMfmaWaves)
 k_tile_rows(int nrb, int nrows, const int *__restrict__ ptr, const int *__restrict__ split,
-            const int *__restrict__ tcol, const VT *__restrict__ tval, const double *__restrict__ x1,
-            int n1, const double *__restrict__ x2, int n2, int ld, const double *__restrict__ base,
+            const int4 *__restrict__ tcol, const VT *__restrict__ tval, const double *__restrict__ x1,
+            const double *__restrict__ x2, int ld, const double *__restrict__ base,
             double c1, double c2, double *__restrict__ out, RedBuf red, const int *__restrict__ run,
             const float *__restrict__ x1f, const float *__restrict__ x2f) {
-  if (run && *run == 0) return;                  // every column of the CG loop has stopped
-  constexpr int H = RB * kT;                     // rows of a block
+  constexpr int NT = TW * kWave;
   const int wv = wave_uniform(), lane = lane_id(), g = lane >> 4, l16 = lane & 15;
   const int rb = xcd_item(blockIdx.x, nrb);
+  // (loaded beside the flag, not after it: one memory round trip less)
+  const int b = ptr[rb], e = ptr[rb + 1], s = split ? split[rb] : e;
+  if (run && *run == 0) return;                  // every column of the CG loop has stopped
   // one accumulator: with both parts, the second part's products enter the
   // same sums with x2 negated when c2 = -c1 (exact), and the total is scaled by
   // c1; a lone part is scaled by its own coefficient.  Only c2 = +-c1 is
   // served with both parts.
-  dbl4 acc[RB][NCB];
+  dbl4 acc[NCB];
 #pragma unroll
-  for (int h = 0; h < RB; ++h)
+  for (int q = 0; q < NCB; ++q)
 #pragma unroll
-    for (int q = 0; q < NCB; ++q)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[h][q][r] = 0.0;
-  const int b = ptr[rb], e = ptr[rb + 1], s = split ? split[rb] : e;
+    for (int r = 0; r < 4; ++r) acc[q][r] = 0.0;
   const double sg2 = (c1 != 0.0 && c2 == -c1) ? -1.0 : 1.0;
-  const int nel = H * ld;
-  constexpr int NF = kMaxLd * H / (kTW * kWave);
+  const int nel = kT * ld;
+  constexpr int NF = (kT * kT * NCB + NT - 1) / NT;   // (ld <= 16 NCB)
   // this thread's output elements; with DOT, their x1 values are loaded now, so
   // that the loads are done when the block's sums are (the dot product then
   // costs no memory round trip after the product)
   double xd[NF];
 #pragma unroll
   for (int u = 0; u < NF; ++u) {
-    const int el = threadIdx.x + u * kTW * kWave;
-    const int lr = el / ld, row = rb * H + lr;
+    const int el = threadIdx.x + u * NT;
+    const int lr = el / ld, row = rb * kT + lr;
     xd[u] = (DOT && el < nel && row < nrows) ? x1[(size_t)row * ld + (el - lr * ld)] : 0.0;
   }
+  // the units are dealt to the waves in turn through both parts, from another
+  // wave in each row block (a wave keeps its SIMD, so the odd units spread)
+  const int w1 = (wv + rb) & (TW - 1), w2 = (w1 - (s - b)) & (TW - 1);
+  auto part1 = [&](auto x) { tile_row_acc<NCB, D>(b + w1, s, TW, tcol, tval, x, ld, 1.0, acc); };
+  auto part2 = [&](auto x) { tile_row_acc<NCB, D>(s + w2, e, TW, tcol, tval, x, ld, sg2, acc); };
   if constexpr (std::is_same<VT, float>::value) {
-    // (x1f, x2f: FP32 copies of x1, x2 -- the products round the slices to
-    // FP32 anyway, so the sums are the same bit for bit, from half the bytes)
-    if (c1 != 0.0) {
-      if (x1f) tile_row_acc_f32<NCB, D, RB>(b + wv, s, kTW, tcol, tval, x1f, n1, ld, 1.0, acc);
-      else tile_row_acc_f32<NCB, D, RB>(b + wv, s, kTW, tcol, tval, x1, n1, ld, 1.0, acc);
-    }
-    if (split && c2 != 0.0) {
-      if (x2f) tile_row_acc_f32<NCB, D, RB>(s + wv, e, kTW, tcol, tval, x2f, n2, ld, sg2, acc);
-      else tile_row_acc_f32<NCB, D, RB>(s + wv, e, kTW, tcol, tval, x2, n2, ld, sg2, acc);
-    }
+    if (c1 != 0.0) x1f ? part1(x1f) : part1(x1);
+    if (split && c2 != 0.0) x2f ? part2(x2f) : part2(x2);
   } else {
-    if (c1 != 0.0) tile_row_acc<NCB, D, RB>(b + wv, s, kTW, tcol, tval, x1, n1, ld, 1.0, acc);
-    if (split && c2 != 0.0) tile_row_acc<NCB, D, RB>(s + wv, e, kTW, tcol, tval, x2, n2, ld, sg2, acc);
+    if (c1 != 0.0) part1(x1);
+    if (split && c2 != 0.0) part2(x2);
   }
   const double cf = c1 != 0.0 ? c1 : c2;
-  __shared__ double part[kTW * H * kT * NCB];    // ld <= 16 NCB
+  __shared__ double part[TW * kT * kT * NCB];    // ld <= 16 NCB
 #pragma unroll
-  for (int h = 0; h < RB; ++h)
+  for (int q = 0; q < NCB; ++q) {
+    const int col = NCB * l16 + q;
 #pragma unroll
-    for (int q = 0; q < NCB; ++q) {
-      const int col = NCB * l16 + q;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int lr = h * kT + acc_row<VT>(g, r);   // row of the block held in register r
-        if (col < ld) part[(wv * H + lr) * ld + col] = cf * acc[h][q][r];
-      }
-    }
+    for (int r = 0; r < 4; ++r)                  // row of the block held in register r
+      if (col < ld) part[(wv * kT + acc_row<VT>(g, r)) * ld + col] = cf * acc[q][r];
+  }
   __syncthreads();
   double fin[NF], vo[NF];
 #pragma unroll
   for (int u = 0; u < NF; ++u) {
-    const int el = threadIdx.x + u * kTW * kWave;
+    const int el = threadIdx.x + u * NT;
     fin[u] = vo[u] = 0.0;
     if (el < nel) {
-      const int lr = el / ld, col = el - lr * ld, row = rb * H + lr;
+      const int lr = el / ld, col = el - lr * ld, row = rb * kT + lr;
       double v = part[el];
 #pragma unroll
-      for (int w = 1; w < kTW; ++w) v += part[w * nel + el];
+      for (int w = 1; w < TW; ++w) v += part[w * nel + el];
       if (row < nrows) {
         const size_t o = (size_t)row * ld + col;
         v += base ? base[o] : 0.0;
@@ -409,22 +369,23 @@ k_tile_rows(int nrb, int nrows, const int *__restrict__ ptr, const int *__restri
   auto store_out = [&]() {
 #pragma unroll
     for (int u = 0; u < NF; ++u) {
-      const int el = threadIdx.x + u * kTW * kWave;
-      const int lr = el / ld, row = rb * H + lr;
+      const int el = threadIdx.x + u * NT;
+      const int lr = el / ld, row = rb * kT + lr;
       if (el < nel && row < nrows) out[(size_t)row * ld + (el - lr * ld)] = vo[u];
     }
   };
   __syncthreads();                               // every wave read its part: reuse it
 #pragma unroll
   for (int u = 0; u < NF; ++u) {
-    const int el = threadIdx.x + u * kTW * kWave;
+    const int el = threadIdx.x + u * NT;
     if (el < nel) part[el] = fin[u];
   }
   __syncthreads();
   if ((int)threadIdx.x < ld) {
     const int c = threadIdx.x;
     double sm = 0.0;
-    for (int lr = 0; lr < H; ++lr) sm += part[lr * ld + c];
+#pragma unroll
+    for (int lr = 0; lr < kT; ++lr) sm += part[lr * ld + c];
     store_partial(red.part2 + (size_t)rb * ld + c, sm);
   }
   const int grp = rb / kPGroup;
@@ -435,7 +396,7 @@ k_tile_rows(int nrb, int nrows, const int *__restrict__ ptr, const int *__restri
   store_out();
   if (!last) return;
   // (read by the next launch: no completion wait)
-  group_sums_store(red.part2, gridDim.x, ld, grp, red.part3, wv, kTW, false);
+  group_sums_store(red.part2, gridDim.x, ld, grp, red.part3, wv, TW, false);
   __syncthreads();
   if (threadIdx.x == 0) reset_counter(cnt);
 }
@@ -480,7 +441,7 @@ template <> struct TileAT<float> {
 };
 
 template <typename MT, int NCB>
-__global__ void __launch_bounds__(kTW * kWave)
+__global__ void __launch_bounds__(kTW * kWave, kMfmaWaves)
 k_dense_tiles(int nall, const int2 *__restrict__ items, const MT *__restrict__ packed,
               const long long *__restrict__ toff, const int *__restrict__ ioff,
               const int *__restrict__ ni, const double *__restrict__ y, int ld,
