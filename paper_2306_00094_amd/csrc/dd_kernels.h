@@ -880,13 +880,6 @@ k_gamma_rows(int nrows, const int *__restrict__ ptr, const int *__restrict__ spl
 // mode 2 (masked init): columns with mask[c] != 0 restart from the residual
 //                  given in q (mode 0 for those columns), the others keep
 //                  their state.
-// mode 3 (residual replacement; RED = 2 only, after a mode-1 launch of the
-//                  same step): the columns that stepped (act_prev and no
-//                  breakdown) take the residual given in q, recomputed from x
-//                  with more accurate operators, as r, and z = D^{-1} r; x and
-//                  p are kept.  The chunk partials of r.z and r.r are those of
-//                  the new residual, so the direction launch that follows
-//                  forms beta, the convergence test and p from it.
 // The last workgroup then updates the column state:
 //   init:   rz = r.z, active = (r.r > stop2) for c < nrhs, iters = 0
 //   update: iters += 1; converged when r.r <= stop2; beta = r.z / rz_old
@@ -899,20 +892,13 @@ k_gamma_rows(int nrows, const int *__restrict__ ptr, const int *__restrict__ spl
 // group finishes the column state from the group sums -- the load of the final
 // sum spread over the groups instead of one workgroup reducing every chunk of
 // every column.
-// RED = 2 (split; mode 1 only): the launch ends with the chunk partials (no
-// completion count); k_cg_direction_state reduces them, in the tree of RED = 1,
-// and finishes the column state.
-// Workgroup 0 records the state this step started from (r.z, active) and its
-// step length and breakdown marks for it.
 template <int E, int RED = 0>
 __global__ void __launch_bounds__(kBlock)
 k_cg_update(int mode, int nrows, int ld, int nrhs, const double *__restrict__ dinv,
             double *__restrict__ x, double *__restrict__ r, double *__restrict__ z,
             double *__restrict__ p, const double *__restrict__ q, RedBuf red, ColState st,
             int use_precond, int *__restrict__ host_nact, int init_p_is_z,
-            const int *__restrict__ mask, int npq, int cpw, float *__restrict__ p32,
-            const int *__restrict__ run) {
-  if (run && *run == 0) return;                       // every column has stopped (see k_tile_rows)
+            const int *__restrict__ mask, int npq, int cpw, float *__restrict__ p32) {
   __shared__ double lds[kRowsE * kMaxLd];
   __shared__ double salpha[kMaxLd];
   __shared__ int sact[kMaxLd];
@@ -945,11 +931,6 @@ k_cg_update(int mode, int nrows, int ld, int nrhs, const double *__restrict__ di
       }
     }
   }
-  if (mode == 3) {
-    for (int c = threadIdx.x; c < ld; c += kBlock) sact[c] = st.act_prev[c] && !st.brk[c];
-    if (blockIdx.x == 0 && threadIdx.x == 0) st.flag[3] = 1;    // read by the direction launch
-    __syncthreads();
-  }
   if (mode == 1) {
     // wave wv takes the columns c0 .. c0+7 of every group of 32 (the loads of a
     // wave's columns overlap; each column's sum is that of partials_sum)
@@ -973,12 +954,6 @@ k_cg_update(int mode, int nrows, int ld, int nrhs, const double *__restrict__ di
         }
         salpha[c] = a;
         sact[c] = act;
-        if (RED == 2 && blockIdx.x == 0) {
-          st.rz_prev[c] = st.rz[c];
-          st.act_prev[c] = st.active[c];
-          st.brk[c] = st.active[c] && !act;
-          st.alpha[c] = a;
-        }
       }
     }
     __syncthreads();
@@ -1002,8 +977,8 @@ k_cg_update(int mode, int nrows, int ld, int nrhs, const double *__restrict__ di
       if (j < nrows) {
         const size_t o = (size_t)j * ld + c;
         const bool init = mode == 0 || (mode == 2 && mask[c]);
-        const bool act = init ? true : ((mode == 1 || mode == 3) && sact[c] != 0);
-        const bool repl = (mode == 2 && init) || (mode == 3 && act);
+        const bool act = init ? true : (mode == 1 && sact[c] != 0);
+        const bool repl = mode == 2 && init;
         double rr_ = repl ? qv[k] : rv[k];
         if (repl) wm[k] |= 2;
         if (mode == 1 && act) {
@@ -1071,10 +1046,6 @@ k_cg_update(int mode, int nrows, int ld, int nrhs, const double *__restrict__ di
       if (lane == 0) __hip_atomic_store(red.part1 + (size_t)(chunk0 + k) * ld + c, sm, __ATOMIC_RELAXED,
                                         __HIP_MEMORY_SCOPE_AGENT);
     }
-  }
-  if constexpr (RED == 2) {                           // the direction launch reduces them
-    flush();
-    return;
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);   // both partial stores complete before the count
   const double *fin0 = red.part0, *fin1 = red.part1;
@@ -1736,181 +1707,6 @@ k_cg_direction(int nrows, int ld, const double *__restrict__ z, double *__restri
       const double pn = fma(st.beta[c], p[e], z[e]);
       p[e] = pn;
       if (p32) p32[e] = (float)pn;      // copy gathered by the FP32-data products
-    }
-  }
-}
-
-// End of a CG step after the split update (k_cg_update<E, 2>).  The column
-// sums of r.z and r.r are formed from the nch chunk partials of the update in
-// one fixed order -- group sums over kPGroup consecutive chunks by the tree of
-// chunk_group_sum (one thread per column, dot and group, the butterfly's pairs
-// added in registers), then the groups in order -- which gives the bits of the
-// grouped update's two levels.  Workgroup b >= 1 updates the direction
-// p = z + beta p of the still iterating columns for column block (b - 1) % ncb
-// (kDirCols columns, or ld when narrower) over its share of the rows, and
-// reduces the sums of that block only; workgroup 0 reduces every column and
-// writes the column state (from the sums and the state the step started from:
-// rz_prev, act_prev, brk, recorded by the update's workgroup 0; the state is
-// read by no other workgroup of this launch), and publishes (active columns +
-// 1) to host_nact; it updates no rows, so its longer reduction runs beside
-// the others' row work.  ld: a power of two from 8 to kMaxLd; the grid 1 plus
-// a multiple of ld / min(ld, kDirCols).  run: as in k_tile_rows; it is st.flag + 1,
-// which workgroup 0 of this launch rewrites.  A workgroup that reads the new
-// value 0 has no active column to update either, so either value gives the
-// same result.
-constexpr int kDirCols = 16;       // 128-byte row segments
-constexpr int kDirBlock = 512;
-constexpr int kDirE = 12;          // direction elements per thread held across the reduction
-
-// tot[t * kMaxLd + c] = sum of dot t (0: r.z, 1: r.r) of column c, c0 <= c < c0 + nc
-// (2 nc dividing kDirBlock); gsum: kDirBlock doubles of LDS.
-__device__ __forceinline__ void direction_sums(const RedBuf &red, int ld, int nch, int c0, int nc, double *gsum,
-                                               double *tot) {
-  const int pairs = 2 * nc, gpp = kDirBlock / pairs;
-  const int ngrp = (nch + kPGroup - 1) / kPGroup;
-  const int q = threadIdx.x % pairs, gi = threadIdx.x / pairs;
-  const int t = q / nc, c = c0 + (q - t * nc);
-  const double *src = (t ? red.part1 : red.part0) + c;
-  double acc = 0.0;                             // (threads q < pairs: the running sum)
-  for (int g0 = 0; g0 < ngrp; g0 += gpp) {
-    const int g = g0 + gi;
-    double s = 0.0;
-    if (g < ngrp) {
-      double u[kPGroup];
-#pragma unroll
-      for (int m = 0; m < kPGroup; ++m) {
-        const int ch = g * kPGroup + m;
-        u[m] = ch < nch ? src[(size_t)ch * ld] : 0.0;
-      }
-#pragma unroll
-      for (int h = kPGroup / 2; h >= 1; h /= 2)
-#pragma unroll
-        for (int m = 0; m < h; ++m) u[m] += u[m + h];
-      s = u[0];
-    }
-    __syncthreads();                            // the last pass's sums are consumed
-    gsum[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x < pairs)
-      for (int i = 0; i < gpp && g0 + i < ngrp; ++i) acc += gsum[i * pairs + threadIdx.x];
-  }
-  if (threadIdx.x < pairs) tot[t * kMaxLd + c] = acc;
-  __syncthreads();
-}
-
-__global__ void __launch_bounds__(kDirBlock)
-k_cg_direction_state(int nrows, int ld, const double *__restrict__ z, double *__restrict__ p, RedBuf red,
-                     ColState st, int nch, int *__restrict__ host_nact, float *__restrict__ p32,
-                     const int *__restrict__ run, double drop2) {
-  if (run && *run == 0) {              // every column had stopped: nothing changes, report none active
-    if (blockIdx.x == 0 && threadIdx.x == 0 && host_nact)
-      __hip_atomic_store(host_nact, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    return;
-  }
-  __shared__ double gsum[kDirBlock];
-  __shared__ double tot[2 * kMaxLd];
-  __shared__ double sbeta[kMaxLd];
-  __shared__ int sact[kMaxLd];
-  __shared__ int sdue[kMaxLd];
-  const int cw = min(ld, kDirCols), ncb = ld / cw;
-  // workgroup 0: every column's sums and state, no direction rows; workgroup
-  // b >= 1: column block (b - 1) % ncb over row share (b - 1) / ncb
-  const bool all = blockIdx.x == 0;
-  const int wb = all ? 0 : (int)blockIdx.x - 1;
-  const int cb = wb % ncb, rr = wb / ncb, nrr = ((int)gridDim.x - 1) / ncb;
-  const int c0 = all ? 0 : cb * cw, nc = all ? ld : cw;
-  // rows [j0, j1) of column block cb; the first kDirE elements per thread are
-  // loaded before the sums, so that their loads overlap the reduction
-  const int per = (nrows + nrr - 1) / nrr;
-  const int j0 = min(nrows, rr * per), j1 = min(nrows, j0 + per);
-  const int n = all ? 0 : (j1 - j0) * cw;
-  auto offset = [&](int i) {
-    const int jr = i / cw;
-    return (size_t)(j0 + jr) * ld + cb * cw + (i - jr * cw);
-  };
-  double zv[kDirE], pv[kDirE];
-#pragma unroll
-  for (int k = 0; k < kDirE; ++k) {
-    const int i = threadIdx.x + k * kDirBlock;
-    zv[k] = pv[k] = 0.0;
-    if (i < n) {
-      const size_t e = offset(i);
-      zv[k] = z[e];
-      pv[k] = p[e];
-    }
-  }
-  direction_sums(red, ld, nch, c0, nc, gsum, tot);
-  if (threadIdx.x < nc) {
-    const int c = c0 + threadIdx.x;
-    const double rz = tot[c], rr2 = tot[kMaxLd + c];
-    const int act0 = st.act_prev[c], brk = st.brk[c];
-    int act = 0;
-    double beta = 0.0;
-    if (act0 && !brk) {
-      beta = rz / st.rz_prev[c];
-      act = rr2 > st.stop2[c] ? 1 : 0;
-    }
-    if (all) {
-      if (act0 && brk) st.flag[0] = 1;            // breakdown: p^T q <= 0
-      if (act0 && !brk) {
-        st.iters[c] += 1;
-        st.beta[c] = beta;
-        st.rz[c] = rz;
-      }
-      // residual replacement: the reference norm after one, and whether the
-      // column is due for the next.  A replaced residual no smaller than the
-      // one replaced before means the directions make no progress on the
-      // true residual (operators too inaccurate for the system): the column
-      // stops, and the FP64 check of its residual decides what follows.
-      double ref = st.ref2[c];
-      if (st.flag[3] && act0 && !brk) {     // replaced in this step
-        if (!(rr2 < ref)) act = 0;
-        ref = rr2;
-        st.ref2[c] = ref;
-      }
-      sdue[c] = (act && rr2 < drop2 * ref) ? 1 : 0;
-      st.active[c] = act;
-      st.nrm2[c] = rr2;
-    }
-    sbeta[c] = beta;
-    sact[c] = act;
-  }
-  __syncthreads();
-  if (all && threadIdx.x < kWave) {
-    const int lane = threadIdx.x;
-    int na = lane < ld ? sact[lane] : 0;
-    int nd = lane < ld ? sdue[lane] : 0;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-      na += __shfl_xor(na, o, kWave);
-      nd += __shfl_xor(nd, o, kWave);
-    }
-    if (lane == 0) {
-      if (st.flag[0]) na = 0;            // breakdown ends the loop
-      st.flag[1] = na > 0 ? 1 : 0;
-      st.flag[2] = (na > 0 && nd > 0) ? 1 : 0;
-      st.flag[3] = 0;
-      if (host_nact) __hip_atomic_store(host_nact, na + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < kDirE; ++k) {
-    const int i = threadIdx.x + k * kDirBlock;
-    const int c = cb * cw + (i & (cw - 1));
-    if (i < n && sact[c]) {
-      const size_t e = offset(i);
-      const double pn = fma(sbeta[c], pv[k], zv[k]);
-      p[e] = pn;
-      if (p32) p32[e] = (float)pn;
-    }
-  }
-  for (int i = threadIdx.x + kDirE * kDirBlock; i < n; i += kDirBlock) {
-    const int c = cb * cw + (i & (cw - 1));
-    if (sact[c]) {
-      const size_t e = offset(i);
-      const double pn = fma(sbeta[c], p[e], z[e]);
-      p[e] = pn;
-      if (p32) p32[e] = (float)pn;
     }
   }
 }

@@ -548,40 +548,23 @@ inline unsigned upd_grid(int n_gamma, int ld) {
   return (ch + w - 1) / w;
 }
 
-// Workgroups of the direction launch that ends a split update: each reduces
-// the chunk partials of its column block (redundantly), so more of them cost
-// L2 reads and fewer of them leave CUs idle for the direction update.  (Its
-// 512-thread workgroups run one per CU.)
-constexpr unsigned kDirStateGrid = 256;
-inline unsigned direction_state_grid(int ld) {
-  const unsigned ncb = (unsigned)(ld / std::min(ld, kDirCols));
-  // workgroup 0 (the column state) and the row workgroups together fill at
-  // most one workgroup per CU: one more would wait for a second round
-  return 1 + ncb * std::max(1u, (kDirStateGrid - 1) / ncb);
-}
-
 // CG update launch; the elements per thread follow from the batch width.
-// red: 0 single-level reduction, 1 grouped, 2 split (mode 1, one chunk per
-// workgroup; the direction launch k_cg_direction_state reduces the chunk
-// partials and finishes the step).
+// red: 0 single-level reduction, 1 grouped (one chunk per workgroup).
 void launch_update(dd_ctx *c, int mode, int ld, int nrhs, const double *dinv, double *x, double *r,
                    double *z, double *p, const double *q, int precond, int *host_nact,
-                   int init_p_is_z, const int *mask, int npq, int red = 0, const int *run = nullptr) {
+                   int init_p_is_z, const int *mask, int npq, int red = 0) {
   if (c->n_gamma <= 0) return;
   const int cpw = upd_cpw(ld);
   const dim3 g(upd_grid(c->n_gamma, ld)), b(kBlock);
   const int E = std::max(1, cpw * kRowsE * ld / kBlock);
   if (cpw != 1) red = 0;
 #define DD_UPD(EE)                                                                                        \
-  if (red == 2)                                                                                           \
-    hipLaunchKernelGGL((k_cg_update<EE, 2>), g, b, 0, c->stream, mode, c->n_gamma, ld, nrhs, dinv, x,      \
-                       r, z, p, q, c->red, c->st, precond, host_nact, init_p_is_z, mask, npq, cpw, c->g32.p, run); \
-  else if (red == 1)                                                                                      \
+  if (red == 1)                                                                                           \
     hipLaunchKernelGGL((k_cg_update<EE, 1>), g, b, 0, c->stream, mode, c->n_gamma, ld, nrhs, dinv, x,      \
-                       r, z, p, q, c->red, c->st, precond, host_nact, init_p_is_z, mask, npq, cpw, c->g32.p, run); \
+                       r, z, p, q, c->red, c->st, precond, host_nact, init_p_is_z, mask, npq, cpw, c->g32.p); \
   else                                                                                                    \
     hipLaunchKernelGGL((k_cg_update<EE>), g, b, 0, c->stream, mode, c->n_gamma, ld, nrhs, dinv, x,         \
-                       r, z, p, q, c->red, c->st, precond, host_nact, init_p_is_z, mask, npq, cpw, c->g32.p, run)
+                       r, z, p, q, c->red, c->st, precond, host_nact, init_p_is_z, mask, npq, cpw, c->g32.p)
   switch (E) {
     case 1: DD_UPD(1); break;
     case 2: DD_UPD(2); break;
@@ -680,6 +663,14 @@ void gamma_apply(dd_ctx *c, int prec, Src p, const double *z, int ld, const doub
 
 // ------------------------------------------------- tiled wide batches --
 // (batches of kTileMinLd or more columns; dd_tiles.h)
+// Whether the interface rows sum p^T q by groups of row blocks (a completion
+// count per group) or leave the block sums to the update, whose every workgroup
+// then reads them all.
+#ifndef DD_DG
+#define DD_DG 640
+#endif
+inline int dot_grouped(int nrb) { return nrb > DD_DG; }
+
 template <typename VT, int NCB, bool DOT>
 void launch_tile_rows_t(dd_ctx *c, bool interface_rows, const VT *val, const double *x1,
                         const double *x2, int ld, const double *base, double c1, double c2,
@@ -690,17 +681,18 @@ void launch_tile_rows_t(dd_ctx *c, bool interface_rows, const VT *val, const dou
   const int *ptr = interface_rows ? c->d_tG_ptr : c->d_tI_ptr;
   const int *split = interface_rows ? c->d_tG_split : nullptr;
   const int4 *col = (const int4 *)(interface_rows ? c->d_tG_col : c->d_tI_col);
-  if (DOT) c->gamma_parts = (nrb + kPGroup - 1) / kPGroup;          // group sums of p^T q
+  const int grouped = dot_grouped(nrb);
+  if (DOT) c->gamma_parts = grouped ? (nrb + kPGroup - 1) / kPGroup : nrb;      // sums of p^T q
   hipEvent_t e0 = nullptr, e1 = nullptr;
   constexpr int kDepth = 2, kWaves = 4;        // units in flight per wave, waves per row block
   constexpr auto kern = k_tile_rows<VT, NCB, DOT, kDepth, kWaves>;
   const dim3 g(nrb), b(kWaves * kWave);
   if (DOT && kernel_events(c, DD_PHASE_GAMMA, &e0, &e1))
     hipExtLaunchKernelGGL(kern, g, b, 0, c->stream, e0, e1, 0, nrb, nrows, ptr, split, col, val, x1, x2, ld, base,
-                          c1, c2, out, c->red, run, x1f, x2f);
+                          c1, c2, out, c->red, run, x1f, x2f, grouped);
   else
     hipLaunchKernelGGL(kern, g, b, 0, c->stream, nrb, nrows, ptr, split, col, val, x1, x2, ld, base, c1, c2, out,
-                       c->red, run, x1f, x2f);
+                       c->red, run, x1f, x2f, grouped);
 }
 
 // out = base + c1 * (tiled K_IG or K_GG) x1 + c2 * (tiled K_GI) x2 with the
@@ -731,14 +723,14 @@ void tile_rows(dd_ctx *c, int prec, bool interface_rows, const double *x1, const
 
 // w = base + sign * B y for the dense interior blocks B (kinv of `prec`, or the
 // FP64 blocks K_II themselves when kii is set).
-// (w32: also an FP32 copy of w when not nullptr)
+// (w32: also an FP32 copy of w when not nullptr; beta: w = B y + beta w_before)
 void dense_tiles(dd_ctx *c, int prec, bool kii, const double *y, int ld, const double *base, double sign,
-                 double *w, const int *run = nullptr, float *w32 = nullptr) {
+                 double *w, const int *run = nullptr, float *w32 = nullptr, const double *beta = nullptr) {
   if (c->n_dit <= 0) return;
   const dim3 g(c->n_dit), b(kTW * kWave);
 #define DD_DT(MT, NCB, BLK)                                                                                \
   hipLaunchKernelGGL((k_dense_tiles<MT, NCB>), g, b, 0, c->stream, c->NI, c->d_dit, (const MT *)(BLK),   \
-                     c->d_toff, c->d_ioff, c->d_ni, y, ld, base, sign, w, run, w32)
+                     c->d_toff, c->d_ioff, c->d_ni, y, ld, base, sign, w, run, w32, beta)
   if (kii || prec == DD_FP64) {
     const void *blk = kii ? (const void *)c->d_kii_t : c->op[DD_FP64].kinv_t;
     if (ld <= 16) DD_DT(double, 1, blk);
@@ -751,6 +743,62 @@ void dense_tiles(dd_ctx *c, int prec, bool kii, const double *y, int ld, const d
     else DD_DT(float, 4, blk);
   }
 #undef DD_DT
+}
+
+// Rows of a slab of the tiled CG's update: its partial sums are read by every
+// workgroup of the direction launch, so large interfaces take large slabs (the
+// peridynamic system's 37 114 rows: 290 slabs of 128); small ones take small
+// slabs, so that the launch fills the chip (5 181 rows: 162 slabs of 32).  The
+// rule looks at the interface only: a column's sums must not depend on the
+// batch.
+inline int tile_slab(int n_gamma) { return n_gamma >= 32768 ? 128 : (n_gamma >= 8192 ? 64 : 32); }
+
+// The update of a tiled CG step (k_tile_update): mode 1 the step (xup: also x),
+// mode 3 residual replacement.
+void tile_update(dd_ctx *c, int mode, bool xup, int ld, const double *dinv, double *x, const double *p,
+                 const double *q, float *z32, const int *run) {
+  const int sr = tile_slab(c->n_gamma), cw = std::min(ld, kTileCols);
+  const dim3 g(grid_for(c->n_gamma, sr) * (ld / cw)), b(kBlock);
+#define DD_TU(SR, CW, X)                                                                                     \
+  hipLaunchKernelGGL((k_tile_update<SR, CW, X>), g, b, 0, c->stream, mode, c->n_gamma, ld, dinv, x, c->w.rG, \
+                     c->w.zG, p, q, c->red, c->st, dot_grouped(c->t_nrbG) ? c->red.part3 : c->red.part2,     \
+                     c->gamma_parts, z32, run)
+#define DD_TUX(SR, CW) \
+  if (xup) DD_TU(SR, CW, true); \
+  else DD_TU(SR, CW, false)
+#define DD_TUC(SR) \
+  if (cw == 8) { DD_TUX(SR, 8); } \
+  else { DD_TUX(SR, 16); }
+  if (sr == 128) { DD_TUC(128) }
+  else if (sr == 64) { DD_TUC(64) }
+  else { DD_TUC(32) }
+#undef DD_TUC
+#undef DD_TUX
+#undef DD_TU
+}
+
+// The end of a tiled CG step (k_tile_direction): column state, x, p and u = K_IG z
+// with the coupling values of `prec`.
+void tile_direction(dd_ctx *c, int prec, bool xup, int ld, double *x, double *p, int *host_nact, float *p32,
+                    const float *z32, double drop2) {
+  const int cw = std::min(ld, kTileCols);
+  const int ndir = (int)grid_for(c->n_gamma, kDirSlab) * (ld / cw);
+  const int nsl = (int)grid_for(c->n_gamma, tile_slab(c->n_gamma));
+  const dim3 g(1 + ndir + c->t_nrbI), b(kBlock);
+#define DD_TDIR(VT, NCB, VAL)                                                                                  \
+  hipLaunchKernelGGL((k_tile_direction<VT, NCB>), g, b, 0, c->stream, c->n_gamma, ld, c->w.zG, p, x,       \
+                     xup ? 1 : 0, c->red, c->st, nsl, host_nact, p32, drop2, c->t_nrbI, c->NI, c->d_tI_ptr, \
+                     (const int4 *)c->d_tI_col, (const VT *)(VAL), c->w.yI, z32)
+  if (prec == DD_FP64) {
+    if (ld <= 16) DD_TDIR(double, 1, c->d_tI_val64);
+    else if (ld <= 32) DD_TDIR(double, 2, c->d_tI_val64);
+    else DD_TDIR(double, 4, c->d_tI_val64);
+  } else {
+    if (ld <= 16) DD_TDIR(float, 1, c->op[prec].tI_val);
+    else if (ld <= 32) DD_TDIR(float, 2, c->op[prec].tI_val);
+    else DD_TDIR(float, 4, c->op[prec].tI_val);
+  }
+#undef DD_TDIR
 }
 
 // ------------------------------------------------ three-launch iteration --
@@ -1223,11 +1271,11 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
                    o.apply != DD_APPLY_TRSM && o.launch != DD_LAUNCH_PERSISTENT &&
                    (cg3 || c->direction_kernel);
   const int sched = (cg3 ? 1 : 0) | (g32 ? 2 : 0) | (tl ? 4 : 0);
-  // tiled mixed path: FP32 copies of p and w for the FP32 unit products
+  // tiled mixed path: FP32 copies of p, z and w for the FP32 unit products
   // (which round their slices to FP32 anyway: the same sums from half the
   // slice bytes)
   const bool s32 = tl && prec == DD_MIXED;
-  float *p32 = s32 ? w.p32 : nullptr, *w32 = s32 ? w.w32 : nullptr;
+  float *p32 = s32 ? w.p32 : nullptr, *w32 = s32 ? w.w32 : nullptr, *z32 = s32 ? w.z32A : nullptr;
   struct ResetG32 { dd_ctx *c; ~ResetG32() { c->g32 = Gather32{}; } } reset_g32{c};
   c->tev_cg3_ld = cg3 ? ld : 0;
   // CG init: x = 0, z = D^-1 r, previous direction 0 (beta = 0)
@@ -1245,6 +1293,8 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
     if (s32) c->g32 = Gather32{nullptr, nullptr, nullptr, w.p32, nullptr, nullptr};
     launch_update(c, 0, ld, nrhs, op.dinv, uG, w.rG, w.zG, pA, w.qG, o.precond, nullptr,
                   dkv, nullptr, 0, tl ? 1 : 0);
+    // K_IG z_0 = K_IG p_0; every later one comes with the direction
+    if (tl) tile_rows<false>(c, prec, false, pA, nullptr, ld, nullptr, 1.0, 0.0, w.yI, c->st.flag + 1, p32);
   }
   HIPCHK(c, hipGetLastError());
   if (o.launch == DD_LAUNCH_PERSISTENT && o.apply != DD_APPLY_TRSM && c->n_gamma > 0) {
@@ -1284,16 +1334,34 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
     // (formed at the K_IG gathers, which also store it into pB for the rest of
     // the iteration; without interiors the interface rows form and store it)
     const bool p_at_gamma = !dk && c->NI == 0;
-    if (tl) {
-      {
-        PhaseTimer t(c, DD_PHASE_KIG);
-        tile_rows<false>(c, prec, false, pA_, nullptr, ld, nullptr, 1.0, 0.0, w.yI, run, p32);
-      }
+    if (tl) {        // (K_IG z is in yI)
       {
         PhaseTimer t(c, DD_PHASE_INTERIOR);
-        dense_tiles(c, prec, false, w.yI, ld, nullptr, 1.0, w.wI, run, w32);
+        dense_tiles(c, prec, false, w.yI, ld, nullptr, 1.0, w.wI, run, w32, c->st.beta);
       }
       tile_rows<true>(c, prec, true, pA_, w.wI, ld, nullptr, 1.0, -1.0, w.qG, run, p32, w32);
+      const double *dinv = o.precond ? op.dinv : nullptr;
+      {
+        PhaseTimer t(c, DD_PHASE_UPDATE);
+        tile_update(c, 1, replace, ld, dinv, uG, pA_, w.qG, z32, run);
+      }
+      if (replace) {
+        // the FP64 residual of the new x, q = g - K_GG x + K_GI K_II^{-1} K_IG x
+        // (q and y are free until the next step, uI until the back
+        // substitution), takes the place of r in every iterating column.  The
+        // launches do nothing unless the last direction launch found a column
+        // whose residual fell by the drop factor since the last replacement
+        // (st.flag[2]).
+        const int *due = c->st.flag + 2;
+        tile_rows<false>(c, DD_FP64, false, uG, nullptr, ld, nullptr, 1.0, 0.0, w.yI, due);
+        dense_tiles(c, DD_FP64, false, w.yI, ld, nullptr, 1.0, uI, due);
+        tile_rows<false>(c, DD_FP64, true, uG, uI, ld, gG, -1.0, 1.0, w.qG, due);
+        tile_update(c, 3, false, ld, dinv, uG, pA_, w.qG, z32, due);
+      }
+      PhaseTimer t(c, DD_PHASE_KIG);
+      tile_direction(c, prec, !replace, ld, uG, pA_, nact_dst, p32, z32, o.replace_drop * o.replace_drop);
+      HIPCHK(c, hipGetLastError());
+      return DD_OK;
     } else {
       {
         PhaseTimer t(c, DD_PHASE_KIG);
@@ -1310,27 +1378,9 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
     {
       PhaseTimer t(c, DD_PHASE_UPDATE);
       launch_update(c, 1, ld, nrhs, op.dinv, uG, w.rG, w.zG, dk ? pA_ : pB_, w.qG, o.precond,
-                    tl ? nullptr : nact_dst, 0, nullptr, c->gamma_parts, tl ? 2 : 0, run);
+                    nact_dst, 0, nullptr, c->gamma_parts);
     }
-    if (tl && replace) {
-      // the FP64 residual of the new x, q = g - K_GG x + K_GI K_II^{-1} K_IG x
-      // (q, y and w are free until the next step), takes the place of r in
-      // every iterating column.  The launches do nothing unless the last
-      // direction launch found a column whose residual fell by the drop
-      // factor since the last replacement (st.flag[2]).
-      const int *due = c->st.flag + 2;
-      tile_rows<false>(c, DD_FP64, false, uG, nullptr, ld, nullptr, 1.0, 0.0, w.yI, due);
-      dense_tiles(c, DD_FP64, false, w.yI, ld, nullptr, 1.0, w.wI, due);
-      tile_rows<false>(c, DD_FP64, true, uG, w.wI, ld, gG, -1.0, 1.0, w.qG, due);
-      launch_update(c, 3, ld, nrhs, op.dinv, uG, w.rG, w.zG, pA_, w.qG, o.precond, nullptr, 0, nullptr, 0,
-                    2, due);
-    }
-    if (tl) {        // the split update's state and the direction in one launch
-      hipLaunchKernelGGL(k_cg_direction_state, dim3(direction_state_grid(ld)), dim3(kDirBlock), 0, c->stream,
-                         c->n_gamma, ld, w.zG,
-                         pA_, c->red, c->st, (int)upd_grid(c->n_gamma, ld), nact_dst, c->g32.p, run,
-                         o.replace_drop * o.replace_drop);
-    } else if (dk) {
+    if (dk) {
       unsigned gd = std::min(4096u, grid_for((size_t)c->n_gamma * ld, kBlock));
       hipLaunchKernelGGL(k_cg_direction, dim3(gd), dim3(kBlock), 0, c->stream, c->n_gamma, ld,
                          w.zG, pA_, c->st, c->g32.p);

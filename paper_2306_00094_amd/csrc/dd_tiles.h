@@ -273,10 +273,10 @@ constexpr int kTW = 4;
 // nullptr; a part whose coefficient is 0 is skipped).  All vectors DD layout
 // with leading dimension ld, out nrows rows.  Wave w takes units b + w, b + w +
 // TW, ...; the wave sums are added in wave order.  With DOT the workgroup also
-// writes x1^T out over its rows (rows in order) per column to red.part2, and
-// the last of every kPGroup consecutive workgroups the group sum to red.part3,
-// which the update kernel reduces (the step length of the CG iteration, from
-// p^T S p).
+// writes x1^T out over its rows per column to red.part2 (the step length of the
+// CG iteration, from p^T S p); grouped: the last of every kPGroup consecutive
+// workgroups also writes the group sum to red.part3, for the update kernel,
+// which otherwise reads the block sums themselves.
 // Bound (interface rows, 2 320 blocks of 45 units, 32 columns, h = 1/160):
 // without the unit and vector loads, matrix instructions and the fixed work of a
 // block (column lists, wave sums, dot product) take 50 of the 66 us in FP64,
@@ -288,18 +288,13 @@ constexpr int kTW = 4;
 // few iterations ahead of the device).  x1f, x2f (FP32 units only; may be
 // nullptr): FP32 copies of x1, x2 whose rows the products load instead.
 template <typename VT, int NCB, bool DOT, int D, int TW>
-__global__ void __launch_bounds__(TW * kWave, kMfmaWaves)
-k_tile_rows(int nrb, int nrows, const int *__restrict__ ptr, const int *__restrict__ split,
-            const int4 *__restrict__ tcol, const VT *__restrict__ tval, const double *__restrict__ x1,
-            const double *__restrict__ x2, int ld, const double *__restrict__ base,
-            double c1, double c2, double *__restrict__ out, RedBuf red, const int *__restrict__ run,
-            const float *__restrict__ x1f, const float *__restrict__ x2f) {
+__device__ __forceinline__ void
+tile_rows_body(int rb, int nrows, int b, int s, int e, bool split, const int4 *__restrict__ tcol,
+               const VT *__restrict__ tval, const double *__restrict__ x1, const double *__restrict__ x2, int ld,
+               const double *__restrict__ base, double c1, double c2, double *__restrict__ out, RedBuf red, int nrb,
+               const float *__restrict__ x1f, const float *__restrict__ x2f, bool grouped) {
   constexpr int NT = TW * kWave;
   const int wv = wave_uniform(), lane = lane_id(), g = lane >> 4, l16 = lane & 15;
-  const int rb = xcd_item(blockIdx.x, nrb);
-  // (loaded beside the flag, not after it: one memory round trip less)
-  const int b = ptr[rb], e = ptr[rb + 1], s = split ? split[rb] : e;
-  if (run && *run == 0) return;                  // every column of the CG loop has stopped
   // one accumulator: with both parts, the second part's products enter the
   // same sums with x2 negated when c2 = -c1 (exact), and the total is scaled by
   // c1; a lone part is scaled by its own coefficient.  Only c2 = +-c1 is
@@ -374,31 +369,349 @@ k_tile_rows(int nrb, int nrows, const int *__restrict__ ptr, const int *__restri
       if (el < nel && row < nrows) out[(size_t)row * ld + (el - lr * ld)] = vo[u];
     }
   };
-  __syncthreads();                               // every wave read its part: reuse it
+  // x1^T out over the block's 16 rows, rows 8 apart added first, then 4, 2, 1: a
+  // thread's elements lie in one column, NT / ld rows apart (those further apart
+  // than that are added in registers), the rest goes through LDS
+  __shared__ double dsum[NT];
+  const int per = max(1, nel / NT);              // elements of a thread
 #pragma unroll
-  for (int u = 0; u < NF; ++u) {
-    const int el = threadIdx.x + u * NT;
-    if (el < nel) part[el] = fin[u];
-  }
+  for (int h = NF / 2; h >= 1; h /= 2)
+    if (h < per)
+#pragma unroll
+      for (int u = 0; u < h; ++u) fin[u] += fin[u + h];
+  dsum[threadIdx.x] = fin[0];
   __syncthreads();
+  double sm = 0.0;
   if ((int)threadIdx.x < ld) {
-    const int c = threadIdx.x;
-    double sm = 0.0;
+    const int R = kT / per;
+    double u[kT];
 #pragma unroll
-    for (int lr = 0; lr < kT; ++lr) sm += part[lr * ld + c];
-    store_partial(red.part2 + (size_t)rb * ld + c, sm);
+    for (int r = 0; r < kT; ++r) u[r] = r < R ? dsum[r * ld + threadIdx.x] : 0.0;
+#pragma unroll
+    for (int h = kT / 2; h >= 1; h /= 2)
+      if (h < R)
+#pragma unroll
+        for (int r = 0; r < h; ++r) u[r] += u[r + h];
+    sm = u[0];
   }
+  if (!grouped) {
+    if ((int)threadIdx.x < ld) red.part2[(size_t)rb * ld + threadIdx.x] = sm;
+    store_out();
+    return;
+  }
+  if ((int)threadIdx.x < ld) store_partial(red.part2 + (size_t)rb * ld + threadIdx.x, sm);
   const int grp = rb / kPGroup;
-  const int members = min(kPGroup, (int)gridDim.x - grp * kPGroup);
+  const int members = min(kPGroup, nrb - grp * kPGroup);
   __shared__ int lflag;
   unsigned *cnt = red.gcount + (size_t)grp * kCounterStride;
   const bool last = last_of(cnt, (unsigned)members, &lflag);
   store_out();
   if (!last) return;
   // (read by the next launch: no completion wait)
-  group_sums_store(red.part2, gridDim.x, ld, grp, red.part3, wv, TW, false);
+  group_sums_store(red.part2, nrb, ld, grp, red.part3, wv, TW, false);
   __syncthreads();
   if (threadIdx.x == 0) reset_counter(cnt);
+}
+
+template <typename VT, int NCB, bool DOT, int D, int TW>
+__global__ void __launch_bounds__(TW * kWave, kMfmaWaves)
+k_tile_rows(int nrb, int nrows, const int *__restrict__ ptr, const int *__restrict__ split,
+            const int4 *__restrict__ tcol, const VT *__restrict__ tval, const double *__restrict__ x1,
+            const double *__restrict__ x2, int ld, const double *__restrict__ base,
+            double c1, double c2, double *__restrict__ out, RedBuf red, const int *__restrict__ run,
+            const float *__restrict__ x1f, const float *__restrict__ x2f, int grouped) {
+  const int rb = xcd_item(blockIdx.x, nrb);
+  // (loaded beside the flag, not after it: one memory round trip less)
+  const int b = ptr[rb], e = ptr[rb + 1], s = split ? split[rb] : e;
+  if (run && *run == 0) return;                  // every column of the CG loop has stopped
+  tile_rows_body<VT, NCB, DOT, D, TW>(rb, nrows, b, s, e, split != nullptr, tcol, tval, x1, x2, ld, base, c1, c2,
+                                      out, red, nrb, x1f, x2f, grouped != 0);
+}
+
+// ------------------------------------------------- vector step of a tiled CG --
+// Between q = S p and the next product the vectors take two passes:
+//   k_tile_update     alpha from the npq p^T q sums pqs; r -= alpha q, z = D^-1 r and
+//                     the partial sums of r.z and r.r;
+//   k_tile_direction  beta from those; x += alpha p, p = z + beta p, the column
+//                     state -- and, in the same launch, u = K_IG z, which needs
+//                     neither: with w_k = K_II^-1 K_IG z_k + beta w_{k-1} (the
+//                     recurrence of p through a linear map; k_dense_tiles adds
+//                     the second term) the K_IG product no longer waits for p.
+// An iteration is four launches (k_dense_tiles, k_tile_rows on the interface
+// rows, these two) instead of five, the row blocks of K_IG run beside the
+// direction's reductions, and the vectors are read and written 9 times instead
+// of 10.  Bound: HBM and the reductions' load latency.  Peridynamic batch (37 114
+// rows x 32 columns): K_IG 21.7 + update 18.9 + direction 12.2 us before, update
+// 9.4 + direction with K_IG 28 us now; fractional system (5 181 x 8): 6.6 + 6.8 +
+// 5.7 us before, 4.8 + 6.2 us now.
+//
+// A workgroup of the update takes kSlab rows x cw columns (cw = min(ld, 16): 128-byte
+// row segments), so narrow systems still fill the chip; a thread keeps one
+// column.  Sums over rows and slabs run in one order for every width.
+constexpr int kTileCols = 16;
+
+// out[t][c] of CW columns from the slab's terms in registers: element k of
+// thread t is row t / CW + k 256 / CW.  Pairs of rows SR / 2 apart are added
+// first, then SR / 4, ...: the levels within a thread, then one thread per
+// column and dot from LDS.  lds: 2 kBlock doubles.
+template <int SR, int CW>
+__device__ __forceinline__ void slab_sums2(double (&a)[SR * CW / kBlock], double (&b)[SR * CW / kBlock], double *lds,
+                                           double *outa, double *outb) {
+  constexpr int E = SR * CW / kBlock, R = kBlock / CW;
+#pragma unroll
+  for (int h = E / 2; h >= 1; h /= 2)
+#pragma unroll
+    for (int k = 0; k < h; ++k) {
+      a[k] += a[k + h];
+      b[k] += b[k + h];
+    }
+  lds[threadIdx.x] = a[0];
+  lds[kBlock + threadIdx.x] = b[0];
+  __syncthreads();
+  if (threadIdx.x < 2 * CW) {
+    const int t = threadIdx.x / CW, c = threadIdx.x % CW;
+    double u[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) u[r] = lds[t * kBlock + r * CW + c];
+#pragma unroll
+    for (int h = R / 2; h >= 1; h /= 2)
+#pragma unroll
+      for (int r = 0; r < h; ++r) u[r] += u[r + h];
+    (t ? outb : outa)[c] = u[0];
+  }
+}
+
+// Sum over i < n of src[i * ld] for column c of the calling thread's column
+// (thread t: column t % cw): sixteen threads take i = 0, 16, .. / 1, 17, .. /
+// ... in order, and every thread of the column adds the sixteen in order.
+// lds: 16 kTileCols doubles, free on entry and on return of the next barrier.
+__device__ __forceinline__ double column_sum(const double *__restrict__ src, int n, int ld, int cw, double *lds) {
+  const int c = threadIdx.x & (cw - 1), gi = threadIdx.x / cw;
+  if (gi < 16) {
+    double s = 0.0;
+    constexpr int U = 8;                         // loads in flight
+    for (int i0 = gi; i0 < n; i0 += 16 * U) {
+      double v[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) v[k] = i0 + 16 * k < n ? src[(size_t)(i0 + 16 * k) * ld + c] : 0.0;
+#pragma unroll
+      for (int k = 0; k < U; ++k) s += v[k];
+    }
+    lds[gi * cw + c] = s;
+  }
+  __syncthreads();
+  double s = lds[c];
+#pragma unroll
+  for (int k = 1; k < 16; ++k) s += lds[k * cw + c];
+  return s;
+}
+
+// mode 1: the step; mode 3: residual replacement (the columns that stepped
+// take the residual given in q; x and p are kept).  XUP: also x += alpha p (a
+// step that is followed by a replacement, which multiplies the new x).  The
+// workgroups of slab 0 record the state the step started from, its step
+// lengths and breakdown marks.
+template <int SR, int CW, bool XUP>
+__global__ void __launch_bounds__(kBlock)
+k_tile_update(int mode, int nrows, int ld, const double *__restrict__ dinv, double *__restrict__ x,
+              double *__restrict__ r, double *__restrict__ z, const double *__restrict__ p,
+              const double *__restrict__ q, RedBuf red, ColState st, const double *__restrict__ pqs, int npq,
+              float *__restrict__ z32, const int *__restrict__ run) {
+  constexpr int E = SR * CW / kBlock, R = kBlock / CW;
+  __shared__ double lds[2 * kBlock];
+  const int ncb = ld / CW, cb = blockIdx.x % ncb, slab = blockIdx.x / ncb;
+  const int c0 = cb * CW, col = c0 + threadIdx.x % CW;
+  const int row0 = slab * SR + threadIdx.x / CW;
+  double rv[E], qv[E], dv[E], xv[E], pv[E];
+  // (the flag is looked at once the loads are under way)
+  const int go = run ? *run : 1;
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    const int j = row0 + k * R;
+    rv[k] = qv[k] = xv[k] = pv[k] = 0.0;
+    dv[k] = 1.0;
+    if (j < nrows) {
+      const size_t o = (size_t)j * ld + col;
+      rv[k] = r[o];
+      qv[k] = q[o];
+      if (XUP && mode == 1) {
+        xv[k] = x[o];
+        pv[k] = p[o];
+      }
+      if (dinv) dv[k] = dinv[j];
+    }
+  }
+  if (go == 0) {                                 // every column has stopped, or none is due (mode 3)
+    if (mode == 1 && slab == 0 && threadIdx.x < CW) st.act_prev[col] = 0;     // no column takes this step
+    return;
+  }
+  int act;
+  double al = 0.0;
+  if (mode == 1) {
+    const double pq = column_sum(pqs + c0, npq, ld, CW, lds);
+    const int act0 = st.active[col];
+    const double rz0 = st.rz[col];
+    act = act0 && pq > 0.0;
+    if (act) al = rz0 / pq;
+    if (slab == 0 && threadIdx.x < CW) {
+      st.rz_prev[col] = rz0;
+      st.act_prev[col] = act0;
+      st.brk[col] = act0 && !act;
+      st.alpha[col] = al;
+    }
+    __syncthreads();                             // the sums are read: lds is reused below
+  } else {
+    act = st.act_prev[col] && !st.brk[col];
+    if (blockIdx.x == 0 && threadIdx.x == 0) st.flag[3] = 1;     // read by the direction launch
+  }
+  double rz[E], rr[E];
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    const int j = row0 + k * R;
+    rz[k] = rr[k] = 0.0;
+    if (j < nrows) {
+      const size_t o = (size_t)j * ld + col;
+      double rn = rv[k];
+      if (act) {
+        rn = mode == 1 ? fma(-al, qv[k], rn) : qv[k];
+        r[o] = rn;
+        if (XUP && mode == 1) x[o] = fma(al, pv[k], xv[k]);
+      }
+      const double zn = dinv ? dv[k] * rn : rn;
+      if (act) {
+        z[o] = zn;
+        if (z32) z32[o] = (float)zn;
+      }
+      rz[k] = rn * zn;
+      rr[k] = rn * rn;
+    }
+  }
+  slab_sums2<SR, CW>(rz, rr, lds, red.part0 + (size_t)slab * ld + c0, red.part1 + (size_t)slab * ld + c0);
+}
+
+// Nothing happens unless some column took the step (act_prev, written by the
+// update; the loop flag itself is rewritten by this launch).  Workgroup 0: the
+// column state of the step from the nsl slab sums (and the state it started
+// from), published to host_nact (active columns + 1); no other workgroup of the
+// launch reads what it writes.  Workgroups 1 .. nrb: u = K_IG z, one row block each
+// (four waves).  The others: x += alpha p (unless the update did: xup = 0) and
+// p = z + beta p over kDirSlab rows x cw columns.  (The row blocks take longest
+// and come first: the short direction workgroups then fill the places beside
+// them.)
+constexpr int kDirSlab = 64;
+template <typename VT, int NCB>
+__global__ void __launch_bounds__(kBlock, kMfmaWaves)
+k_tile_direction(int nrows, int ld, const double *__restrict__ z, double *__restrict__ p,
+                 double *__restrict__ x, int xup, RedBuf red, ColState st, int nsl, int *__restrict__ host_nact,
+                 float *__restrict__ p32, double drop2, int nrb, int nI,
+                 const int *__restrict__ ptr, const int4 *__restrict__ tcol, const VT *__restrict__ tval,
+                 double *__restrict__ u, const float *__restrict__ z32) {
+  const bool none = __ballot(lane_id() < ld && st.act_prev[lane_id()] != 0) == 0;    // no column stepped
+  if (blockIdx.x > 0 && (int)blockIdx.x <= nrb) {
+    const int rb = xcd_item((int)blockIdx.x - 1, nrb);
+    const int b = ptr[rb], e = ptr[rb + 1];
+    if (none) return;
+    tile_rows_body<VT, NCB, false, 2, 4>(rb, nI, b, e, e, false, tcol, tval, z, nullptr, ld, nullptr, 1.0, 0.0, u,
+                                         red, nrb, z32, nullptr, false);
+    return;
+  }
+  __shared__ double lds[16 * kTileCols];
+  const int cw = min(ld, kTileCols), ncb = ld / cw;
+  if (blockIdx.x > 0) {
+    constexpr int E = kDirSlab * kTileCols / kBlock;
+    const int d = (int)blockIdx.x - 1 - nrb, cb = d % ncb, slab = d / ncb;
+    const int col = cb * cw + (threadIdx.x & (cw - 1)), R = kBlock / cw;
+    const int row0 = slab * kDirSlab + threadIdx.x / cw, row1 = min(nrows, (slab + 1) * kDirSlab);
+    const int act0 = st.act_prev[col], brk = st.brk[col];
+    const double rzp = st.rz_prev[col], al = st.alpha[col];
+    double zv[E], pv[E], xv[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int j = row0 + k * R;
+      zv[k] = pv[k] = xv[k] = 0.0;
+      if (j < row1) {
+        const size_t o = (size_t)j * ld + col;
+        zv[k] = z[o];
+        pv[k] = p[o];
+        if (xup) xv[k] = x[o];
+      }
+    }
+    if (none) return;
+    const double rz = column_sum(red.part0 + cb * cw, nsl, ld, cw, lds);
+    if (!act0 || brk) return;
+    const double beta = rz / rzp;
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int j = row0 + k * R;
+      if (j < row1) {
+        const size_t o = (size_t)j * ld + col;
+        const double pn = fma(beta, pv[k], zv[k]);
+        p[o] = pn;
+        if (p32) p32[o] = (float)pn;
+        if (xup) x[o] = fma(al, pv[k], xv[k]);
+      }
+    }
+    return;
+  }
+  // workgroup 0: the column state
+  if (none) {                                    // every column had stopped: nothing changes, report none active
+    if (threadIdx.x == 0 && host_nact) __hip_atomic_store(host_nact, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return;
+  }
+  __shared__ int sact[kMaxLd], sdue[kMaxLd];
+  for (int cb = 0; cb < ncb; ++cb) {
+    const double rz = column_sum(red.part0 + cb * cw, nsl, ld, cw, lds);
+    __syncthreads();
+    const double rr = column_sum(red.part1 + cb * cw, nsl, ld, cw, lds);
+    __syncthreads();
+    if ((int)threadIdx.x < cw) {
+      const int c = cb * cw + threadIdx.x;
+      const int act0 = st.act_prev[c], brk = st.brk[c];
+      int act = 0;
+      double beta = 0.0;
+      if (act0 && brk) st.flag[0] = 1;           // breakdown: p^T q <= 0
+      // residual replacement: the reference norm after one, and whether the
+      // column is due for the next.  A replaced residual no smaller than the
+      // one replaced before means the directions make no progress on the
+      // true residual (operators too inaccurate for the system): the column
+      // stops, and the FP64 check of its residual decides what follows.
+      double ref = st.ref2[c];
+      if (act0 && !brk) {
+        beta = rz / st.rz_prev[c];
+        act = rr > st.stop2[c] ? 1 : 0;
+        st.iters[c] += 1;
+        st.rz[c] = rz;
+        if (st.flag[3]) {                        // replaced in this step
+          if (!(rr < ref)) act = 0;
+          ref = rr;
+          st.ref2[c] = ref;
+        }
+      }
+      st.beta[c] = beta;
+      sdue[c] = (act && rr < drop2 * ref) ? 1 : 0;
+      sact[c] = act;
+      st.active[c] = act;
+      st.nrm2[c] = rr;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    const int lane = threadIdx.x;
+    int na = lane < ld ? sact[lane] : 0;
+    int nd = lane < ld ? sdue[lane] : 0;
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+      na += __shfl_xor(na, o, kWave);
+      nd += __shfl_xor(nd, o, kWave);
+    }
+    if (lane == 0) {
+      if (st.flag[0]) na = 0;                    // breakdown ends the loop
+      st.flag[1] = na > 0 ? 1 : 0;
+      st.flag[2] = (na > 0 && nd > 0) ? 1 : 0;
+      st.flag[3] = 0;
+      if (host_nact) __hip_atomic_store(host_nact, na + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
 }
 
 // Interior solve w = base + sign * K_II^-1 y on the matrix cores (or, with the
@@ -411,7 +724,8 @@ k_tile_rows(int nrb, int nrows, const int *__restrict__ ptr, const int *__restri
 // row, zero padded).  Wave w applies the tiles J = w, w + kTW, ... to the
 // 16-row slices of y; the wave sums are added in wave order.  FP64 blocks:
 // v_mfma_f64_16x16x4f64; FP32 blocks (mixed path): v_mfma_f32_16x16x4f32 with
-// FP32 operands and accumulation, the wave sums added in FP64.
+// FP32 operands and accumulation, the wave sums added in FP64.  beta (may be
+// nullptr): w += beta w_before per column (the CG's recurrence, k_tile_direction).
 template <typename MT> struct DenseAcc;
 template <> struct DenseAcc<double> {
   typedef dbl4 acc_t;
@@ -446,13 +760,25 @@ k_dense_tiles(int nall, const int2 *__restrict__ items, const MT *__restrict__ p
               const long long *__restrict__ toff, const int *__restrict__ ioff,
               const int *__restrict__ ni, const double *__restrict__ y, int ld,
               const double *__restrict__ base, double sign, double *__restrict__ w,
-              const int *__restrict__ run, float *__restrict__ w32) {
-  if (run && *run == 0) return;                  // every column of the CG loop has stopped
+              const int *__restrict__ run, float *__restrict__ w32, const double *__restrict__ beta) {
   const int wv = wave_uniform(), lane = lane_id(), g = lane >> 4, l16 = lane & 15;
   const int2 item = items[blockIdx.x];
+  if (run && *run == 0) return;                  // every column of the CG loop has stopped
   if (item.x < 0) return;                        // padding of a short XCD list
   const int k = item.x, r0 = item.y * kT;
   const int n = ni[k], i0 = ioff[k];
+  // this thread's previous w and beta, loaded early
+  constexpr int NF = kT * kT * NCB / (kTW * kWave);      // (ld <= 16 NCB)
+  double wp[NF], bt[NF];
+#pragma unroll
+  for (int u = 0; u < NF; ++u) {
+    const int el = threadIdx.x + u * kTW * kWave, lr = el / ld, row = r0 + lr;
+    wp[u] = bt[u] = 0.0;
+    if (beta && el < kT * ld && row < n) {
+      bt[u] = beta[el - lr * ld];
+      wp[u] = w[(size_t)(i0 + row) * ld + (el - lr * ld)];
+    }
+  }
   const int nt = (n + kT - 1) / kT;
   const MT *A = packed + toff[k] + (size_t)item.y * nt * 256;
   // y rows past the block (the next subdomain's, or the last row repeated at
@@ -510,16 +836,19 @@ k_dense_tiles(int nall, const int2 *__restrict__ items, const MT *__restrict__ p
   }
   __syncthreads();
   const int nel = kT * ld;
-  for (int el = threadIdx.x; el < nel; el += kTW * kWave) {
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const int el = threadIdx.x + f * kTW * kWave;
     const int lr = el / ld, c = el - lr * ld, row = r0 + lr;
-    if (row < n) {
+    if (el < nel && row < n) {
       double v = part[el];
 #pragma unroll
       for (int u = 1; u < kTW; ++u) v += part[u * nel + el];
       const size_t o = (size_t)(i0 + row) * ld + c;
-      const double wv2 = (base ? base[o] : 0.0) + sign * v;
-      w[o] = wv2;
-      if (w32) w32[o] = (float)wv2;          // FP32 copy for the FP32 unit products
+      double wn = (base ? base[o] : 0.0) + sign * v;
+      if (bt[f] != 0.0) wn = fma(bt[f], wp[f], wn);      // (beta = 0: w holds nothing yet)
+      w[o] = wn;
+      if (w32) w32[o] = (float)wn;           // FP32 copy for the FP32 unit products
     }
   }
 }
