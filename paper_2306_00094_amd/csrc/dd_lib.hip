@@ -22,6 +22,7 @@
 #include "dd_tiles.h"
 #include "dd_assemble.h"
 #include "dd_persistent.h"
+#include "dd_direct.h"
 
 using namespace dd;
 
@@ -46,6 +47,8 @@ struct Ops {
   void *tI_val = nullptr;  // units of K_IG (T), wide batches
   void *tG_val = nullptr;  // units of [K_GG | K_GI] (T), wide batches
   void *kinv_t = nullptr;  // K_II^{-1} packed into 16x16 tiles (T), wide batches
+  double *sd = nullptr;    // dense S of a small interface (n_gamma x direct_ld), formed on first use
+  bool sd_ready = false;
   bool ready = false;
 };
 
@@ -166,9 +169,11 @@ struct dd_ctx {
     int apply = 0, launch = 0, dk = 0, check_every = 0, cg3 = 1;
     double ms = 0, inner_tol = 0;
     double drop = 0;            // mixed, replacing schedule: the replacement drop factor
+    bool direct = false;        // one-launch CG on the dense S
   };
   int force_cg3 = -1;         // autotuner: -1 schedule decides, else the schedule bits (bit 0 three
                               // launches, bit 1 FP32 gathers)
+  int force_direct = -1;      // autotuner: the same for the one-launch CG
   Tuned tuned[2][7];
   // continuous batching
   struct Batch {
@@ -422,6 +427,8 @@ size_t footprint_bytes(const dd_problem *p, dd_precision prec, int max_nrhs) {
     b += kp * 8 + kp * s + (p->n_sub + 1) * 8;
     if (prec == DD_MIXED) b += kp * 8;  // the FP64 fallback's packed inverse
   }
+  if (p->n_sub > 0 && p->n_gamma <= kDirectMax && NI <= (size_t)kDirectMaxNI)     // dense S of a small interface
+    b += (size_t)p->n_gamma * direct_ld(p->n_gamma) * 8 * (prec == DD_MIXED ? 2 : 1);
   b += (12 * (size_t)p->n_gamma + 6 * NI) * ld * 8;                   // work vectors
   b += (4 * (size_t)p->n_gamma + NI) * ld * 4;                        // FP32 gather copies
   size_t chunks = std::max<size_t>((p->n_gamma + kGChunk - 1) / kGChunk,
@@ -1044,6 +1051,11 @@ dd_status factor_impl(dd_ctx *c, int pi) {
   return DD_OK;
 }
 
+// The one-launch CG on the dense S (dd_direct.h) serves this system.
+bool can_direct(const dd_ctx *c) {
+  return c->n_gamma > 0 && c->n_gamma <= kDirectMax && c->NI > 0 && c->NI <= kDirectMaxNI && !c->classic_cg;
+}
+
 dd_status ensure_ops(dd_ctx *c, int pi) {
   Ops &o = c->op[pi];
   if (o.L) return DD_OK;
@@ -1062,6 +1074,7 @@ dd_status ensure_ops(dd_ctx *c, int pi) {
   TRY(al((void **)&o.diag, c->n_gamma * 8));
   TRY(al((void **)&o.dinv, c->n_gamma * 8));
   if (c->tiles) TRY(al(&o.kinv_t, (size_t)c->t_kpack * s));
+  if (can_direct(c)) TRY(al((void **)&o.sd, (size_t)c->n_gamma * direct_ld(c->n_gamma) * 8));
   if (pi == DD_FP64) {
     o.ig_val = c->d_ig_val64;
     o.g_val = c->d_g_val64;
@@ -1171,7 +1184,47 @@ struct CoreOpts {
   int cg3;        // bit 0: three launches per CG iteration where possible; bit 1: FP32 gathers (mixed)
   int reliable = 0;   // DD_MIXED, tiled: iterations between FP64 residual replacements (0: none)
   double replace_drop = 0.0;   // residual reduction after which a column is due for one
+  bool direct = false;         // one-launch CG on the dense S
 };
+
+// One-launch CG of a small interface: x = S^-1 r (w.rG) per column, S formed on
+// the first call after a factorisation.
+dd_status direct_cg(dd_ctx *c, int prec, int ld, int nrhs, const CoreOpts &o, double *x) {
+  Ops &op = c->op[prec];
+  const int N = c->n_gamma, Np = direct_ld(N);
+  if (!op.sd_ready) {
+    const size_t lds = (size_t)c->NI * sizeof(double);
+    if (prec == DD_FP64)
+      hipLaunchKernelGGL((k_direct_schur<double, double>), dim3(N), dim3(kSchurBlock), lds, c->stream, N, Np, c->NI,
+                         c->d_g_ptr, c->d_g_split, c->d_g_col, (const double *)op.g_val, (const double *)op.kinv,
+                         c->d_koff, c->d_ioff, c->d_ni, c->d_rowsub, op.sd);
+    else
+      hipLaunchKernelGGL((k_direct_schur<float, float>), dim3(N), dim3(kSchurBlock), lds, c->stream, N, Np, c->NI,
+                         c->d_g_ptr, c->d_g_split, c->d_g_col, (const float *)op.g_val, (const float *)op.kinv,
+                         c->d_koff, c->d_ioff, c->d_ni, c->d_rowsub, op.sd);
+    HIPCHK(c, hipGetLastError());
+    op.sd_ready = true;
+  }
+  HIPCHK(c, hipMemsetAsync(c->st.flag, 0, sizeof(int), c->stream));      // no breakdown yet
+  const double *dinv = o.precond ? op.dinv : nullptr;
+  PhaseTimer t(c, DD_PHASE_LOOP);
+  auto launch = [&](auto r) {
+    constexpr int R = decltype(r)::value;
+    hipLaunchKernelGGL(k_direct_cg<R>, dim3(ld), dim3(kDirectBlock), 0, c->stream, N, op.sd, ld, nrhs, dinv, c->w.rG,
+                       x, c->st, o.max_it);
+  };
+  switch (Np / kWave) {
+    case 1: launch(std::integral_constant<int, 1>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    case 3: launch(std::integral_constant<int, 3>{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 5: launch(std::integral_constant<int, 5>{}); break;
+    default: launch(std::integral_constant<int, kDirectRows>{}); break;
+  }
+  HIPCHK(c, hipGetLastError());
+  return DD_OK;
+}
+
 
 // Untuned solves run three launches per iteration (k_cg_kig) at every batch
 // width, so a column's arithmetic never depends on the batch.  The autotuner
@@ -1258,6 +1311,15 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
   } else {
     interior_solve(c, prec, o.apply, bI, w.wI, ld);
     gamma_apply(c, prec, plain(nullptr), w.wI, ld, bG, 0.0, -1.0, w.rG);
+  }
+  if (o.direct) {
+    c->tev_cg3_ld = 0;
+    c->last_launch = DD_LAUNCH_PERSISTENT;
+    TRY(direct_cg(c, prec, ld, nrhs, o, uG));
+    kig_apply(c, prec, plain(uG), ld, bI, -1.0, w.yI);
+    interior_solve(c, prec, o.apply, w.yI, uI, ld);
+    HIPCHK(c, hipGetLastError());
+    return DD_OK;
   }
   // Three launches per iteration where the interiors exist and their inverse
   // is applied (k_cg_kig); otherwise four (K_IG, interior solve, interface
@@ -2028,7 +2090,7 @@ dd_status dd_factor(dd_ctx *c, dd_precision prec) {
   if (prec != DD_FP64 && prec != DD_MIXED) return fail(c, DD_EINVAL, "unknown precision");
   c->err.clear();
   TRY(ensure_ops(c, prec));
-  c->op[prec].ready = false;
+  c->op[prec].ready = c->op[prec].sd_ready = false;
   return prec == DD_FP64 ? factor_impl<double>(c, DD_FP64) : factor_impl<float>(c, DD_MIXED);
 }
 
@@ -2095,7 +2157,7 @@ dd_status dd_autotune(dd_ctx *c, dd_precision prec, int32_t nrhs, const dd_solve
   hipLaunchKernelGGL(k_fill_rhs, dim3(256), dim3(256), 0, c->stream, c->n_dof, nrhs, c->n_dof,
                      0x5eedull, b);
   HIPCHK(c, hipGetLastError());
-  struct Cand { int apply, launch, dk, ce, cg3; double drop = 0.0; };
+  struct Cand { int apply, launch, dk, ce, cg3; double drop = 0.0; bool direct = false; };
   std::vector<Cand> cands;
   // three-launch iteration (when there are interiors), then the four-launch
   // one with the direction formed at the gathers or kept by its own kernel
@@ -2131,6 +2193,8 @@ dd_status dd_autotune(dd_ctx *c, dd_precision prec, int32_t nrhs, const dd_solve
       cands.push_back({DD_APPLY_INV, DD_LAUNCH_GRAPH, 1, 4, 4});
     }
   }
+  if (can_direct(c))       // one launch runs the whole CG (reported as a persistent launch)
+    cands.push_back({DD_APPLY_INV, DD_LAUNCH_AUTO, 0, 0, 0, 0.0, true});
   cands.push_back({DD_APPLY_TRSM, DD_LAUNCH_KERNELS, 0, 2, 0});
   // The cooperative persistent launch is timed only on request
   // (DD_TUNE_PERSISTENT=1): it has never won, and its first launch creates the
@@ -2151,6 +2215,7 @@ dd_status dd_autotune(dd_ctx *c, dd_precision prec, int32_t nrhs, const dd_solve
     if (cd.drop > 0.0) oc.inner_tol = cd.drop;
     c->direction_kernel = cd.dk;
     c->force_cg3 = cd.cg3;
+    c->force_direct = cd.direct ? 1 : 0;
     dd_status s = dd_solve(c, prec, b, u, nrhs, c->n_dof, &oc, nullptr);   // warm-up (captures graphs)
     if (s != DD_OK && s != DD_ENOCONV) continue;
     const int reps = 3;
@@ -2179,6 +2244,7 @@ dd_status dd_autotune(dd_ctx *c, dd_precision prec, int32_t nrhs, const dd_solve
       oc.inner_tol = itol;
       c->direction_kernel = bc.dk;
       c->force_cg3 = bc.cg3;
+      c->force_direct = bc.direct ? 1 : 0;
       dd_status s = dd_solve(c, prec, b, u, nrhs, c->n_dof, &oc, nullptr);
       if (s != DD_OK) continue;
       const int reps = 3;
@@ -2195,7 +2261,7 @@ dd_status dd_autotune(dd_ctx *c, dd_precision prec, int32_t nrhs, const dd_solve
     }
   }
   c->direction_kernel = saved_dk;
-  c->force_cg3 = -1;
+  c->force_cg3 = c->force_direct = -1;
   c->err.clear();
   const double best_drop = replaces ? bc.drop : 0.0;
   auto &t = c->tuned[prec][lg];
@@ -2203,6 +2269,7 @@ dd_status dd_autotune(dd_ctx *c, dd_precision prec, int32_t nrhs, const dd_solve
   t.set = true;
   t.apply = bc.apply;
   t.launch = bc.launch;
+  t.direct = bc.direct;
   t.dk = bc.dk;
   t.cg3 = bc.cg3;
   t.check_every = bc.ce;
@@ -2210,7 +2277,7 @@ dd_status dd_autotune(dd_ctx *c, dd_precision prec, int32_t nrhs, const dd_solve
   t.inner_tol = prec == DD_MIXED ? best_itol : 0.0;
   if (out) {
     out->apply = bc.apply;
-    out->launch = bc.launch;
+    out->launch = bc.direct ? DD_LAUNCH_PERSISTENT : bc.launch;
     out->direction_kernel = bc.dk;
     out->check_every = bc.ce;
     out->ms_per_solve = best;
@@ -2572,6 +2639,9 @@ dd_status dd_solve(dd_ctx *c, dd_precision prec, const double *b_dev, double *u_
   if (prec == DD_MIXED) o.inner_tol = resolve_inner_tol(c, prec, L, o.inner_tol);
   int use_cg3 = 1;
   double tuned_drop = 0.0;
+  // small interfaces run the one-launch CG unless a launch mode is asked for
+  // (or the autotuner found another schedule faster)
+  bool direct = o.launch == DD_LAUNCH_AUTO && can_direct(c);
   struct RestoreDk {
     dd_ctx *c;
     int v;
@@ -2587,6 +2657,7 @@ dd_status dd_solve(dd_ctx *c, dd_precision prec, const double *b_dev, double *u_
         o.launch = t.launch;
         c->direction_kernel = t.dk;
         use_cg3 = t.cg3;
+        direct = t.direct && can_direct(c);
         if (o.check_every == 0) o.check_every = t.check_every;
       }
     }
@@ -2602,7 +2673,9 @@ dd_status dd_solve(dd_ctx *c, dd_precision prec, const double *b_dev, double *u_
               o.check_every,
               (o.launch == DD_LAUNCH_PERSISTENT || o.launch == DD_LAUNCH_GRAPH) ? o.launch : DD_LAUNCH_KERNELS,
               use_cg3};
+  if (c->force_direct >= 0) direct = c->force_direct != 0;
   const bool tl = use_tiles(c, co.cg3, L, co.apply, co.launch);
+  co.direct = direct && !tl && !(co.cg3 & 2) && co.apply == DD_APPLY_INV && !c->direction_kernel;
   // residual replacement in the mixed solve (tiled path, FP64 operators formed)
   if (prec == DD_MIXED && o.reliable != 0) co.reliable = o.reliable < 0 ? kReplacePeriod : o.reliable;
   co.replace_drop = itol_requested > 0.0 ? itol_requested : (tuned_drop > 0.0 ? tuned_drop : kReplaceDrop);
