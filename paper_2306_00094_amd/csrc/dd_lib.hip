@@ -1981,10 +1981,10 @@ dd_status dd_setup(const dd_problem *p, void *hip_stream, int32_t max_nrhs, dd_c
       c->err = "hipMemset failed";
       return bail(DD_EHIP);
     }
-    hipLaunchKernelGGL(k_fill_units, dim3(grid_for(NI, kWave)), dim3(kWave), 0, c->stream, NI, c->d_ig_ptr,
+    hipLaunchKernelGGL(k_fill_units, dim3(c->t_nrbI), dim3(kT * kT), 0, c->stream, NI, c->d_ig_ptr,
                        (const int *)nullptr, c->d_ig_col, c->d_ig_val64, c->d_tI_ptr, (const int *)nullptr,
                        c->d_tI_col, c->d_tI_val64);
-    hipLaunchKernelGGL(k_fill_units, dim3(grid_for(c->n_gamma, kWave)), dim3(kWave), 0, c->stream, c->n_gamma,
+    hipLaunchKernelGGL(k_fill_units, dim3(c->t_nrbG), dim3(kT * kT), 0, c->stream, c->n_gamma,
                        c->d_g_ptr, c->d_g_split, c->d_g_col, c->d_g_val64, c->d_tG_ptr, c->d_tG_split, c->d_tG_col,
                        c->d_tG_val64);
     if ((s = upload(c, &c->d_dit, items.data(), items.size())) != DD_OK) return bail(s);

@@ -63,32 +63,48 @@ constexpr int kUV = kT * kT;
 // column kk = t % 16 of unit t / 16 is step kk / 4 of lane group kk % 4.
 __host__ __device__ constexpr int unit_slot(int t) { return t / kT * kT + t % 4 * 4 + t % kT / 4; }
 
-// Values of a CSR matrix into its (zeroed) FP64 units: one thread per row, which
-// finds each entry's column in its block's list (units [tptr, tsplit) hold
-// the entries [ptr, split), units [tsplit, tptr + 1) the others; split and tsplit
-// may be nullptr) and adds the entries in order.
-__global__ void __launch_bounds__(kWave)
+// Values of a CSR matrix into its (zeroed) FP64 units, one workgroup per row
+// block, 16 lanes per row: a lane finds its entries' columns in the block's list
+// (units [tptr, tsplit) hold the entries [ptr, split), units [tsplit, tptr + 1) the
+// others; split and tsplit may be nullptr).  A row that repeats a column (or
+// lists its columns out of order) is left to one lane, which adds its entries
+// in order.  Bound: the latency of the searches, in LDS where the list fits
+// (one thread per row, searching in memory, took 1.6 ms on the peridynamic
+// interface rows, this 0.28 ms).
+constexpr int kFillList = 4096;
+__global__ void __launch_bounds__(kT * kT)
 k_fill_units(int nrows, const int *__restrict__ ptr, const int *__restrict__ split, const int *__restrict__ col,
              const double *__restrict__ val, const int *__restrict__ tptr, const int *__restrict__ tsplit,
              const int *__restrict__ tcol, double *__restrict__ unit) {
-  const int i = blockIdx.x * kWave + threadIdx.x;
-  if (i >= nrows) return;
-  const int rb = i / kT, ii = i % kT;
+  __shared__ int lds[kFillList];
+  const int rb = blockIdx.x, ii = threadIdx.x / kT, lane = threadIdx.x % kT, i = rb * kT + ii;
   const int t0 = tptr[rb], t2 = tptr[rb + 1], t1 = tsplit ? tsplit[rb] : t2;
-  const int e = ptr[i + 1], mid = split ? split[i] : e;
-  for (int a = ptr[i]; a < e; ++a) {
+  const bool in_lds = (t2 - t0) * kT <= kFillList;
+  if (in_lds)
+    for (int k = threadIdx.x; k < (t2 - t0) * kT; k += kT * kT) lds[k] = tcol[(size_t)t0 * kT + unit_slot(k)];
+  __syncthreads();
+  if (i >= nrows) return;
+  const int b = ptr[i], e = ptr[i + 1], mid = split ? split[i] : e;
+  auto place = [&](int a) {
     const int u0 = a < mid ? t0 : t1, u1 = a < mid ? t1 : t2, c = col[a];
-    const int *list = tcol + (size_t)u0 * kT;
     int lo = 0, hi = (u1 - u0) * kT - 1;          // first place of c
     while (lo < hi) {
       const int m = (lo + hi) / 2;
-      if (list[unit_slot(m)] < c) lo = m + 1;
+      const int cm = in_lds ? lds[(u0 - t0) * kT + m] : tcol[(size_t)u0 * kT + unit_slot(m)];
+      if (cm < c) lo = m + 1;
       else hi = m;
     }
     const int kk = lo % kT;
     // U[ii][kk] is held by lane (kk % 4) * 16 + ii at step kk / 4
     unit[((size_t)u0 + lo / kT) * kUV + TileLayout<double>::pos((kk % 4) * kT + ii, kk / 4)] += val[a];
-  }
+  };
+  bool repeats = false;
+  for (int a = b + 1 + lane; a < e; a += kT) repeats |= a != mid && col[a] <= col[a - 1];
+  for (int o = 1; o < kT; o *= 2) repeats |= __shfl_xor((int)repeats, o) != 0;
+  if (!repeats)
+    for (int a = b + lane; a < e; a += kT) place(a);
+  else if (lane == 0)
+    for (int a = b; a < e; ++a) place(a);
 }
 
 // FP64 tiles -> the FP32 copies of the mixed path (the same values rounded, in
