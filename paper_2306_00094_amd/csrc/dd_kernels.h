@@ -2215,19 +2215,23 @@ k_potrf_panel(T *__restrict__ blocks, const long long *__restrict__ koff,
 // Workgroups take tickets t = J * n_sub + k in the order they start, so a
 // workgroup only ever waits for block columns of smaller tickets, which have
 // already started: the waits cannot deadlock whatever the residency.  A
-// finished block column is written with device-coherent stores, waited for
-// (vmcnt 0) and published in done[k * ntmax + J]; its tile (J+1, J) is
-// published first in done[(n_sub + k) * ntmax + J], which is all the next
-// column's diagonal tile needs, so that column factors its diagonal block
-// while this one is still storing the rest.  Readers poll the flags with
-// device-coherent loads (64 flags per poll) and read the columns the same way,
-// so no cache write-back or invalidate is involved.  Every poll is bounded:
-// after `spin` sleeps (kFlowSpin unless the host sets a smaller limit) the wave
-// raises *timeout and stops waiting, so the launch always drains (the factor
-// is then garbage and the host reports it).
-// A non-positive pivot raises status[k] = column + 1 unless a smaller column
-// of the same subdomain already did: the status store of column J settles
-// before J's early flag, which column J+1 waits for before its own pivots.
+// The factor goes to its own buffer, which the host sets to all ones before the
+// launch (a NaN that arithmetic does not produce): a tile is ready once none of
+// its values is all ones, so the values are their own flags.  They are written
+// with device-coherent stores and polled with device-coherent loads; no flag is
+// waited for or seen after them, no block column is waited for as a whole, and
+// no cache write-back or invalidate is involved.  Every poll is bounded: after
+// `spin` sleeps (kFlowSpin unless the host sets a smaller limit) the wave raises
+// *timeout and stops waiting, so the launch always drains (the factor is then
+// garbage and the host reports it).
+// Before the diagonal block is ready a wave subtracts the last finished column
+// from its first tile only: those four tiles are what the next columns wait for.
+// A non-positive pivot raises status[k] to column + 1, the smallest of a
+// subdomain's columns kept.
+// Bound: the chain of block columns (pivots and inverse of the diagonal block,
+// one product, one store seen by another workgroup): 7.5 us each in FP64, against 12.5
+// us with flags per column, square root, division and a separate substitution
+// for the inverse.
 constexpr int kFlowSpin = 1 << 18;
 // Value of v in lane l (l uniform) as a wave-uniform scalar.
 __device__ __forceinline__ double bcast_lane(double v, int l) {
@@ -2247,11 +2251,13 @@ template <typename T>
 __device__ __forceinline__ void store_coherent(T *p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ bool all_ones(double v) { return __double_as_longlong(v) == -1ll; }
+__device__ __forceinline__ bool all_ones(float v) { return __float_as_int(v) == -1; }
 template <typename T, int OWN>
 __global__ void __launch_bounds__(kBlock, kMfmaWaves)
-k_potrf_flow(T *__restrict__ blocks, const long long *__restrict__ koff, const int *__restrict__ ni,
-             int n_sub, int ntmax, int *__restrict__ status, unsigned *__restrict__ ticket,
-             int *__restrict__ done, int *__restrict__ timeout, T *__restrict__ Xd, int spin) {
+k_potrf_flow(const double *__restrict__ blocks, T *__restrict__ factor, const long long *__restrict__ koff,
+             const int *__restrict__ ni, int n_sub, int *__restrict__ status, unsigned *__restrict__ ticket,
+             int *__restrict__ timeout, T *__restrict__ Xd, int spin) {
   typedef typename Vec4<T>::type V4;
   __shared__ int s_ticket;
   __shared__ T D[16][17];                    // diagonal block, then its factor
@@ -2262,9 +2268,8 @@ k_potrf_flow(T *__restrict__ blocks, const long long *__restrict__ koff, const i
   const int k = s_ticket % n_sub, J = s_ticket / n_sub;
   const int n = ni[k], nt = (n + 15) / 16;
   if (J >= nt) return;
-  T *A = blocks + koff[k];                   // column-major: A[i][j] at j * n + i
-  int *dk = done + (size_t)k * ntmax;                       // column finished
-  int *ek = done + (size_t)(n_sub + k) * ntmax;             // its first tile below the diagonal stored
+  const double *K = blocks + koff[k];        // column-major: K[i][j] at j * n + i
+  T *A = factor + koff[k];
   const int lane = lane_id(), c = lane % 16, g = lane / 16, w = wave_id();
   const int cj = 16 * J + c;
   V4 acc[OWN];
@@ -2274,65 +2279,50 @@ k_potrf_flow(T *__restrict__ blocks, const long long *__restrict__ koff, const i
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int row = 16 * I + acc_row(T(0), g, r);
-      acc[m][r] = (I < nt && row < n && cj < n) ? A[(size_t)cj * n + row] : T(0);
+      acc[m][r] = (I < nt && row < n && cj < n) ? (T)K[(size_t)cj * n + row] : T(0);
     }
   }
-  // wait until block column Q is finished (flags polled 64 at a time), bounded
-  int avail = 0;                             // block columns known finished
+  // values t = 0 .. 3 of row `row` in columns 16 Q + 4 g + t; get() issues the
+  // loads, wait() repeats them until the tile is ready (bounded)
   bool waited_out = false;
-  auto wait_done = [&](int Q) {
-    if (Q < avail) return;
-    unsigned long long fin = 0;
+  auto get = [&](int Q, int row, T (&v)[4]) {
+    const T *col = A + (size_t)(16 * Q + 4 * g) * n + row;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] = row < n ? load_coherent(col + (size_t)t * n) : T(0);
+  };
+  auto wait = [&](int Q, int row, T (&v)[4]) {
     for (int it = 0;; ++it) {
-      const int f = (Q + lane < J) ? load_coherent(dk + Q + lane) : 0;
-      fin = __ballot(f != 0);
-      if ((fin & 1ull) || waited_out) break;
+      bool set = true;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) set = set && !all_ones(v[t]);
+      if (waited_out || __all(set)) break;
       if (it >= spin) {
         waited_out = true;
         if (lane == 0) store_coherent(timeout, 1);
         break;
       }
-      __builtin_amdgcn_s_sleep(2);
+      __builtin_amdgcn_s_sleep(1);
+      get(Q, row, v);
     }
-    avail = waited_out ? J : Q + (~fin == 0ull ? 64 : __builtin_ctzll(~fin));
   };
-  // subtract L[I][Q] L[J][Q]^T from the row tiles m0 <= m < m1 of this wave
+  // subtract L[I][Q] L[J][Q]^T from the row tiles m0 <= m < m1 of this wave (the
+  // next tile's loads are under way while one is waited for)
   auto update = [&](int Q, int m0, int m1) {
-    const T *col = A + (size_t)(16 * Q + 4 * g) * n;
-    T b[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) b[t] = cj < n ? load_coherent(col + (size_t)t * n + cj) : T(0);
+    T b[4], a[2][4];
+    get(Q, cj, b);
 #pragma unroll
     for (int m = 0; m < OWN; ++m) {
-      const int I = J + w + 4 * m;
-      if (m >= m0 && m < m1 && I < nt) {
-        const int row = 16 * I + c;
-        T a[4];
+      if (m < m0 || m >= m1 || J + w + 4 * m >= nt) continue;
+      if (m == m0) get(Q, 16 * (J + w + 4 * m) + c, a[m & 1]);
+      if (m + 1 < m1 && J + w + 4 * (m + 1) < nt) get(Q, 16 * (J + w + 4 * (m + 1)) + c, a[(m + 1) & 1]);
+      if (m == m0) wait(Q, cj, b);
+      wait(Q, 16 * (J + w + 4 * m) + c, a[m & 1]);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) a[t] = row < n ? -load_coherent(col + (size_t)t * n + row) : T(0);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[m] = mfma16x16x4(a[t], b[t], acc[m]);
-      }
+      for (int t = 0; t < 4; ++t) acc[m] = mfma16x16x4(-a[m & 1][t], b[t], acc[m]);
     }
   };
-  for (int Q = 0; Q + 1 < J; ++Q) {
-    wait_done(Q);
-    update(Q, 0, OWN);
-  }
-  if (J > 0 && w == 0) {
-    // the diagonal tile needs only tile (J, J-1) of the last column, which its
-    // owner publishes (early flag) before the rest of that column
-    for (int it = 0;; ++it) {
-      if (waited_out || load_coherent(ek + J - 1) != 0) break;
-      if (it >= spin) {
-        waited_out = true;
-        if (lane == 0) store_coherent(timeout, 1);
-        break;
-      }
-      __builtin_amdgcn_s_sleep(2);
-    }
-    update(J - 1, 0, 1);
-  }
+  for (int Q = 0; Q + 1 < J; ++Q) update(Q, 0, OWN);
+  if (J > 0) update(J - 1, 0, 1);
   const int kb = min(16, n - 16 * J);
   if (w == 0) {
 #pragma unroll
@@ -2340,25 +2330,27 @@ k_potrf_flow(T *__restrict__ blocks, const long long *__restrict__ koff, const i
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     // Cholesky of the diagonal block in registers: lane l < 16 holds row l;
-    // step j broadcasts the pivot and column j lane by lane (v_readlane).  Entries right of
-    // the diagonal become garbage and are never read.
-    T a[16], rd[16];
+    // step j broadcasts the pivot and column j lane by lane (v_readlane).  Entries
+    // right of the diagonal become garbage and are never read.  Lane 16 + c starts
+    // as column c of the identity and takes the same steps -- scaled by the
+    // reciprocal pivot, less column j of the factor times that -- which is the
+    // forward substitution for column c of the inverse (identity past the
+    // block's end).
+    T a[16];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) a[q] = D[lane % 16][q];
+    for (int q = 0; q < 16; ++q) a[q] = lane < 16 ? D[lane % 16][q] : T(q == lane - 16 ? 1 : 0);
     int fail = 0;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      rd[j] = T(1);                          // identity past the block's end
       if (j < kb) {
         T d = bcast_lane(a[j], j);
         if (!(d > T(0))) {
           if (fail == 0) fail = 16 * J + j + 1;
           d = T(1);
         }
-        const T piv = sqrt(d);
-        rd[j] = T(1) / piv;
-        if (lane == j) a[j] = piv;
-        else if (lane > j) a[j] *= rd[j];
+        const T rd = rsqrt(d);
+        if (lane == j) a[j] = d * rd;
+        else if (lane > j) a[j] *= rd;
 #pragma unroll
         for (int m = j + 1; m < 16; ++m) {
           const T lmj = bcast_lane(a[j], m);
@@ -2371,33 +2363,19 @@ k_potrf_flow(T *__restrict__ blocks, const long long *__restrict__ koff, const i
     if (lane < 16) {
 #pragma unroll
       for (int q = 0; q < 16; ++q) D[lane][q] = q < lane ? a[q] : (q == lane && lane < kb ? a[q] : T(0));
+    } else if (lane < 32) {
+#pragma unroll
+      for (int q = 0; q < 16; ++q) Di[q][lane - 16] = a[q];
     }
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // column `lane` of the inverse by forward substitution (reciprocal pivots)
-    T y[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      T v = T(i == lane ? 1 : 0);
-#pragma unroll
-      for (int q = 0; q < i; ++q) v -= D[i][q] * y[q];
-      y[i] = v * rd[i];
-    }
-    if (lane < 16) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) Di[i][lane] = y[i];
-    }
-    if (fail && lane == 0 && load_coherent(status + k) == 0) store_coherent(status + k, fail);
-    for (int e = lane; e < 256; e += kWave) {
-      const int i = e % 16, j = e / 16;
-      if (i < kb && j < kb && i >= j) store_coherent(A + (size_t)(16 * J + j) * n + 16 * J + i, D[i][j]);
+    if (fail && lane == 0) {
+      int seen = load_coherent(status + k);
+      while ((seen == 0 || seen > fail) && !__hip_atomic_compare_exchange_strong(
+                 status + k, &seen, fail, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+      }
     }
   }
-  if (J > 0) {                               // the rest of the last column's update
-    wait_done(J - 1);
-    update(J - 1, w == 0 ? 1 : 0, OWN);
-  }
-  if (w == 0) __builtin_amdgcn_s_waitcnt(0x0F70);   // the status store settles before the early flag
   __syncthreads();
   if (Xd && w == 0) {
     T *Xk = Xd + koff[k];
@@ -2412,6 +2390,7 @@ k_potrf_flow(T *__restrict__ blocks, const long long *__restrict__ koff, const i
 #pragma unroll
   for (int m = 0; m < OWN; ++m) {
     const int I = J + w + 4 * m;
+    if (m > 0 && J > 0) update(J - 1, m, m + 1);
     if (I > J && I < nt) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) S[w][acc_row(T(0), g, r)][c] = acc[m][r];
@@ -2433,15 +2412,13 @@ k_potrf_flow(T *__restrict__ blocks, const long long *__restrict__ koff, const i
         const int colj = 16 * J + acc_row(T(0), g, r);
         if (row < n && colj < n) store_coherent(A + (size_t)colj * n + row, z[r]);
       }
-      if (w == 1 && m == 0) {                // tile (J+1, J): early flag of this column
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        if (lane == 0) store_coherent(ek + J, 1);
-      }
     }
   }
-  __builtin_amdgcn_s_waitcnt(0x0F70);        // vmcnt(0): this thread's stores are done
-  __syncthreads();
-  if (threadIdx.x == 0) store_coherent(dk + J, 1);
+  if (w == 0)                                // the diagonal block (zeros above the diagonal)
+    for (int e = lane; e < 256; e += kWave) {
+      const int i = e % 16, j = e / 16;
+      if (i < kb && j < kb) store_coherent(A + (size_t)(16 * J + j) * n + 16 * J + i, D[i][j]);
+    }
 }
 
 // Trailing update of panel J: A22 -= L21 L21^T on the 16x16 lower tiles of

@@ -147,7 +147,7 @@ struct dd_ctx {
   int gather32 = 0;           // 1: untuned mixed three-launch solves gather FP32 vector copies
   int tune_persistent = 0;    // 1: the autotuner also times the cooperative persistent launch
   Gather32 g32{};             // FP32 gather copies of the three-launch iteration being launched
-  int *d_flow = nullptr;      // single-launch Cholesky: ticket, timeout, done flags
+  int *d_flow = nullptr;      // single-launch Cholesky: ticket, timeout
   double *fac_x = nullptr, *fac_packed = nullptr, *fac_dloc = nullptr;   // factor work space
   bool packed_ready = false;
   int num_cu = 0;
@@ -887,10 +887,10 @@ bool launch_potrf_flow(dd_ctx *c, T *L, T *Xd) {
   const int ntmax = (c->max_ni + 15) / 16, need = (ntmax + 3) / 4;
   const dim3 grid((unsigned)(c->n_sub * ntmax)), blk(kBlock);
   unsigned *ticket = (unsigned *)c->d_flow;
-  int *timeout = c->d_flow + 1, *done = c->d_flow + 2;
+  int *timeout = c->d_flow + 1;
 #define DD_FLOW(OWN)                                                                                  \
-  hipLaunchKernelGGL((k_potrf_flow<T, OWN>), grid, blk, 0, c->stream, L, c->d_koff, c->d_ni, c->n_sub, \
-                     ntmax, c->d_status, ticket, done, timeout, Xd, c->flow_spin)
+  hipLaunchKernelGGL((k_potrf_flow<T, OWN>), grid, blk, 0, c->stream, c->d_kii64, L, c->d_koff, c->d_ni,  \
+                     c->n_sub, c->d_status, ticket, timeout, Xd, c->flow_spin)
   if (need <= 2) DD_FLOW(2);
   else if (need <= 4) DD_FLOW(4);
   else if (need <= 6) DD_FLOW(6);
@@ -907,13 +907,7 @@ template <typename T>
 dd_status factor_impl(dd_ctx *c, int pi) {
   Ops &o = c->op[pi];
   T *L = (T *)o.L, *Kinv = (T *)o.kinv;
-  // copy (and convert) K_II into the factor buffer
-  size_t n = (size_t)c->ktot;
-  if (pi == DD_FP64)
-    hipLaunchKernelGGL((k_copy<double>), dim3(1024), dim3(256), 0, c->stream, n, c->d_kii64, (double *)L);
-  else
-    hipLaunchKernelGGL(k_to_f32, dim3(1024), dim3(256), 0, c->stream, n, c->d_kii64, (float *)L);
-  HIPCHK(c, hipGetLastError());
+  const size_t n = (size_t)c->ktot;
   // work space of the MFMA inverse path, kept for later factorisations: X = L^{-1}
   // (FP64-sized, serves both precisions), K_IG packed into strips (packed once:
   // the values do not change after setup), per-subdomain diag(S) parts
@@ -934,13 +928,19 @@ dd_status factor_impl(dd_ctx *c, int pi) {
   bool flow = false;
   if (c->use_mfma && c->n_sub > 0 && !c->panel_potrf) {
     // one launch; it also writes the diagonal blocks of X
-    HIPCHK(c, hipMemsetAsync(c->d_flow, 0, (2 + 2 * (size_t)c->n_sub * ntmax) * sizeof(int), c->stream));
+    HIPCHK(c, hipMemsetAsync(c->d_flow, 0, 2 * sizeof(int), c->stream));
+    HIPCHK(c, hipMemsetAsync(L, 0xff, n * sizeof(T), c->stream));
     flow = launch_potrf_flow<T>(c, L, panel_trtri ? X : nullptr);
     HIPCHK(c, hipGetLastError());
   }
   if (!flow) {
-    // panel by panel: the diagonal block and the rows below it (one workgroup per
+    // K_II copied (and converted) into the factor buffer, then panel by panel: the diagonal block and the rows below it (one workgroup per
     // subdomain), then the trailing update of all subdomains' tiles
+    if (pi == DD_FP64)
+      hipLaunchKernelGGL((k_copy<double>), dim3(1024), dim3(256), 0, c->stream, n, c->d_kii64, (double *)L);
+    else
+      hipLaunchKernelGGL(k_to_f32, dim3(1024), dim3(256), 0, c->stream, n, c->d_kii64, (float *)L);
+    HIPCHK(c, hipGetLastError());
     for (int J = 0; J < ntmax; ++J) {
       hipLaunchKernelGGL((k_potrf_panel<T>), dim3(c->n_sub), dim3(kBlock), 0, c->stream, L, c->d_koff,
                          c->d_ni, c->d_status, J);
@@ -2056,7 +2056,7 @@ dd_status dd_setup(const dd_problem *p, void *hip_stream, int32_t max_nrhs, dd_c
   }
   if ((s = dalloc(c, &c->red.counter, 8)) != DD_OK) return bail(s);
   if ((s = dalloc(c, &c->d_status, c->n_sub)) != DD_OK) return bail(s);
-  if ((s = dalloc(c, &c->d_flow, 2 + 2 * (size_t)c->n_sub * ((c->max_ni + 15) / 16))) != DD_OK) return bail(s);
+  if ((s = dalloc(c, &c->d_flow, 2)) != DD_OK) return bail(s);
   if ((s = dalloc(c, &c->d_bar, 4)) != DD_OK) return bail(s);
   if ((s = dalloc(c, &c->batch.d_mask, kMaxLd)) != DD_OK) return bail(s);
   if ((s = dalloc(c, &c->d_solve_mask, kMaxLd)) != DD_OK) return bail(s);
