@@ -2854,78 +2854,92 @@ __global__ void k_pack_strips(long long n, const double *__restrict__ val,
     atomicAdd(packed + pos[a], val[a]);      // repeated (row, column) entries add up
 }
 
-// One workgroup per strip item (k, J, K_first, K_last), the first and last row
-// tiles of strip J that hold nonzeros (k < 0: padding, nothing to do).  W's row tiles I < K_first are zero;
-// row tile I >= K_first sums X[I][K] V[K][J] over K_first <= K <= min(I, K_last)
-// (X is lower triangular).  The row tiles go round-robin to the waves; each
-// lane adds the squares of its accumulator rows, the lanes of one column and
+// One workgroup per item (k, J, K_first, K_last): the strips J .. J + kStrips - 1 of
+// subdomain k (those that exist) and the first and last row tiles that hold
+// nonzeros of theirs (k < 0: padding, nothing to do).  W's row tiles I < K_first
+// are zero; row tile I >= K_first sums X[I][K] V[K][J] over K_first <= K <= min(I,
+// K_last) (X is lower triangular).  The row tiles go round-robin to the waves;
+// each lane adds the squares of its accumulator rows, the lanes of one column and
 // then the waves are combined in a fixed order, so dloc[goff[k] + 16 J + c]
 // (column 16 J + c of subdomain k's local interface) has the same bits on
 // every run.  X in the factor's precision, W in FP64.
+// Bound: the reads of X through the L2, once per item: with two strips sharing
+// them, in 16-byte loads, 73 us on the peridynamic system and 86 us on the constant
+// kernel (h = 1/128, FP32), against 126 and 207 us strip by strip (four strips: 40
+// us more, too few workgroups).
+constexpr int kStrips = 2;
 template <typename T>
 __global__ void __launch_bounds__(kBlock, kMfmaWaves)
 k_schur_wsq(const T *__restrict__ X, const double *__restrict__ packed,
             const long long *__restrict__ koff, const long long *__restrict__ voff,
             const int *__restrict__ ni, const int *__restrict__ goff, const int4 *__restrict__ items,
             double *__restrict__ dloc) {
-  __shared__ double part[kWavesPerBlock][16];
+  typedef typename Vec4<T>::type V4;
+  typedef V4 V4u __attribute__((aligned(sizeof(T))));
+  __shared__ double part[kWavesPerBlock][kStrips * 16];
   const int4 it = items[blockIdx.x];
   if (it.x < 0) return;                      // padding of the XCD-interleaved item list
   const int k = it.x, J = it.y, kf = it.z, kl = it.w;
-  const int n = ni[k], nt = (n + 15) / 16;
+  const int n = ni[k], nt = (n + 15) / 16, ng = goff[k + 1] - goff[k], ns = (ng + 15) / 16;
   const int lane = lane_id(), c = lane % 16, g = lane / 16, w = wave_id();
   const T *Xk = X + koff[k];
-  const double *V = packed + voff[k] + (size_t)J * nt * 256 + 4 * lane;
-  double ssq = 0.0;
+  const double *V[kStrips];
+#pragma unroll
+  for (int s = 0; s < kStrips; ++s)          // (past the last strip: that strip again, not stored)
+    V[s] = packed + voff[k] + (size_t)min(J + s, ns - 1) * nt * 256 + 4 * lane;
+  double ssq[kStrips];
+#pragma unroll
+  for (int s = 0; s < kStrips; ++s) ssq[s] = 0.0;
   for (int I = kf + w; I < nt; I += kWavesPerBlock) {
     const int row = 16 * I + c;
-    const T *xr = Xk + (size_t)(row < n ? row : 0) * n;
-    dbl4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
+    const T *xr = Xk + (size_t)(row < n ? row : n - 1) * n;       // (rows past the end are left out below)
+    dbl4 acc[kStrips][2];
+#pragma unroll
+    for (int s = 0; s < kStrips; ++s)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[s][0][r] = acc[s][1][r] = 0.0;
     const int ke = I < kl ? I : kl;
-    int K = kf;
-    for (; K + 1 <= ke; K += 2) {            // two row tiles per step: their loads go out together
-      const int q = 16 * K + 4 * g;
-      const dbl4 b0 = *reinterpret_cast<const dbl4 *>(V + (size_t)K * 256);
-      const dbl4 b1 = *reinterpret_cast<const dbl4 *>(V + (size_t)(K + 1) * 256);
-      double a[8];
+    auto mma = [&](int K, const V4 &a) {
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int qt = q + (t < 4 ? t : 12 + t);
-        a[t] = (row < n && qt < n) ? (double)xr[qt] : 0.0;
+      for (int s = 0; s < kStrips; ++s) {
+        const dbl4 b = *reinterpret_cast<const dbl4 *>(V[s] + (size_t)K * 256);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[s][t & 1] = mfma16x16x4((double)a[t], b[t], acc[s][t & 1]);
       }
-      acc0 = mfma16x16x4(a[0], b0[0], acc0);
-      acc1 = mfma16x16x4(a[1], b0[1], acc1);
-      acc0 = mfma16x16x4(a[2], b0[2], acc0);
-      acc1 = mfma16x16x4(a[3], b0[3], acc1);
-      acc0 = mfma16x16x4(a[4], b1[0], acc0);
-      acc1 = mfma16x16x4(a[5], b1[1], acc1);
-      acc0 = mfma16x16x4(a[6], b1[2], acc0);
-      acc1 = mfma16x16x4(a[7], b1[3], acc1);
+    };
+    int K = kf;
+    const int kw = min(ke + 1, n / 16);      // whole tiles of 16 columns
+    for (; K + 1 < kw; K += 2) {             // two tiles per step: their loads go out together
+      const V4 a0 = *reinterpret_cast<const V4u *>(xr + 16 * K + 4 * g);
+      const V4 a1 = *reinterpret_cast<const V4u *>(xr + 16 * K + 16 + 4 * g);
+      mma(K, a0);
+      mma(K + 1, a1);
     }
-    if (K <= ke) {
+    for (; K <= ke; ++K) {
       const int q = 16 * K + 4 * g;
-      const dbl4 b = *reinterpret_cast<const dbl4 *>(V + (size_t)K * 256);
-      double a[4];
+      V4 a;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) a[t] = (row < n && q + t < n) ? (double)xr[q + t] : 0.0;
-      acc0 = mfma16x16x4(a[0], b[0], acc0);
-      acc1 = mfma16x16x4(a[1], b[1], acc1);
-      acc0 = mfma16x16x4(a[2], b[2], acc0);
-      acc1 = mfma16x16x4(a[3], b[3], acc1);
+      for (int t = 0; t < 4; ++t) a[t] = q + t < n ? xr[q + t] : T(0);
+      mma(K, a);
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const double v = acc0[r] + acc1[r];
-      ssq += v * v;
-    }
+    for (int s = 0; s < kStrips; ++s)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double v = 16 * I + g + 4 * r < n ? acc[s][0][r] + acc[s][1][r] : 0.0;
+        ssq[s] += v * v;
+      }
   }
-  ssq += __shfl_xor(ssq, 16, kWave);
-  ssq += __shfl_xor(ssq, 32, kWave);
-  if (g == 0) part[w][c] = ssq;
+#pragma unroll
+  for (int s = 0; s < kStrips; ++s) {
+    ssq[s] += __shfl_xor(ssq[s], 16, kWave);
+    ssq[s] += __shfl_xor(ssq[s], 32, kWave);
+    if (g == 0) part[w][16 * s + c] = ssq[s];
+  }
   __syncthreads();
-  if (threadIdx.x < 16) {
+  if (threadIdx.x < 16 * kStrips) {
     const int t = threadIdx.x, jl = 16 * J + t;
-    if (jl < goff[k + 1] - goff[k]) dloc[goff[k] + jl] = (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]);
+    if (jl < ng) dloc[goff[k] + jl] = (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]);
   }
 }
 static_assert(kWavesPerBlock == 4, "k_schur_wsq combines four waves");

@@ -1853,8 +1853,14 @@ dd_status dd_setup(const dd_problem *p, void *hip_stream, int32_t max_nrhs, dd_c
           kl[J] = std::max(kl[J], K);
           vpos.push_back(voff[k] + ((long long)J * nt + K) * 256 + ((i % 16) / 4 * 16 + jl % 16) * 4 + i % 4);
         }
-      for (int J = 0; J < ns; ++J)
-        if (kl[J] >= 0) items.push_back(make_int4(k, J, kf[J], kl[J]));
+      for (int J = 0; J < ns; J += kStrips) {
+        int f = INT_MAX, l = -1;
+        for (int t = J; t < std::min(ns, J + kStrips); ++t) {
+          f = std::min(f, kf[t]);
+          l = std::max(l, kl[t]);
+        }
+        if (l >= 0) items.push_back(make_int4(k, J, f, l));
+      }
     }
     {
       // Workgroup b runs on XCD b % 8 (round-robin dispatch), and each XCD has
