@@ -1918,7 +1918,9 @@ __global__ void k_cols_update(size_t n, int ld, double a, const double *__restri
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
        e += (size_t)gridDim.x * blockDim.x) {
     int c = (int)(e % ld);
-    if (mask[c]) y[e] = a * y[e] + (x ? x[e] : 0.0);
+    if (!mask[c]) continue;
+    const double v = x ? x[e] : 0.0;
+    y[e] = a == 0.0 ? v : a * y[e] + v;       // (a = 0: y may hold anything, NaN included)
   }
 }
 
