@@ -678,21 +678,22 @@ void gamma_apply(dd_ctx *c, int prec, Src p, const double *z, int ld, const doub
 #endif
 inline int dot_grouped(int nrb) { return nrb > DD_DG; }
 
-template <typename VT, int NCB, bool DOT>
+template <typename VT, int NCB, bool DOT, bool WIDE>
 void launch_tile_rows_t(dd_ctx *c, bool interface_rows, const VT *val, const double *x1,
                         const double *x2, int ld, const double *base, double c1, double c2,
                         double *out, const int *run, const float *x1f, const float *x2f) {
+  // (WIDE: the step behind these products is k_cg_update, which reads group sums)
   const int nrb = interface_rows ? c->t_nrbG : c->t_nrbI;
   const int nrows = interface_rows ? c->n_gamma : c->NI;
   if (nrb <= 0) return;
   const int *ptr = interface_rows ? c->d_tG_ptr : c->d_tI_ptr;
   const int *split = interface_rows ? c->d_tG_split : nullptr;
   const int4 *col = (const int4 *)(interface_rows ? c->d_tG_col : c->d_tI_col);
-  const int grouped = dot_grouped(nrb);
+  const int grouped = WIDE || dot_grouped(nrb);
   if (DOT) c->gamma_parts = grouped ? (nrb + kPGroup - 1) / kPGroup : nrb;      // sums of p^T q
   hipEvent_t e0 = nullptr, e1 = nullptr;
   constexpr int kDepth = 2, kWaves = 4;        // units in flight per wave, waves per row block
-  constexpr auto kern = k_tile_rows<VT, NCB, DOT, kDepth, kWaves>;
+  constexpr auto kern = k_tile_rows<VT, NCB, DOT, kDepth, kWaves, WIDE>;
   const dim3 g(nrb), b(kWaves * kWave);
   if (DOT && kernel_events(c, DD_PHASE_GAMMA, &e0, &e1))
     hipExtLaunchKernelGGL(kern, g, b, 0, c->stream, e0, e1, 0, nrb, nrows, ptr, split, col, val, x1, x2, ld, base,
@@ -706,22 +707,26 @@ void launch_tile_rows_t(dd_ctx *c, bool interface_rows, const VT *val, const dou
 // coupling values of `prec` (interface_rows: [K_GG | K_GI], else K_IG).  With
 // both parts c2 must be c1 or -c1 (the kernel sums both parts in one
 // accumulator).
-// (x1f, x2f: FP32 copies of x1, x2 for the FP32 units; nullptr: none)
+// (x1f, x2f: FP32 copies of x1, x2 for the FP32 units, nullptr: none; wide: FP32
+// units with FP64 products and sums)
 template <bool DOT>
 void tile_rows(dd_ctx *c, int prec, bool interface_rows, const double *x1, const double *x2, int ld,
                const double *base, double c1, double c2, double *out, const int *run = nullptr,
-               const float *x1f = nullptr, const float *x2f = nullptr) {
+               const float *x1f = nullptr, const float *x2f = nullptr, bool wide = false) {
   // FP64 values straight from the setup copies: the FP64 residual of the mixed
   // path runs on contexts whose FP64 operators were never formed
   const void *v = prec == DD_FP64 ? (interface_rows ? (const void *)c->d_tG_val64 : (const void *)c->d_tI_val64)
                                   : (interface_rows ? c->op[prec].tG_val : c->op[prec].tI_val);
 #define DD_TR(NCB)                                                                                     \
   if (prec == DD_FP64)                                                                                 \
-    launch_tile_rows_t<double, NCB, DOT>(c, interface_rows, (const double *)v, x1, x2, ld, base, c1, c2, out, run, \
-                                         nullptr, nullptr);                                            \
+    launch_tile_rows_t<double, NCB, DOT, false>(c, interface_rows, (const double *)v, x1, x2, ld, base, c1, c2,     \
+                                                out, run, nullptr, nullptr);                           \
+  else if (wide)                                                                                       \
+    launch_tile_rows_t<float, NCB, DOT, true>(c, interface_rows, (const float *)v, x1, x2, ld, base, c1, c2, out,   \
+                                              run, x1f, x2f);                                          \
   else                                                                                                 \
-    launch_tile_rows_t<float, NCB, DOT>(c, interface_rows, (const float *)v, x1, x2, ld, base, c1, c2, out, run, \
-                                        x1f, x2f)
+    launch_tile_rows_t<float, NCB, DOT, false>(c, interface_rows, (const float *)v, x1, x2, ld, base, c1, c2, out,  \
+                                               run, x1f, x2f)
   if (ld <= 16) { DD_TR(1); }
   else if (ld <= 32) { DD_TR(2); }
   else { DD_TR(4); }
@@ -732,17 +737,23 @@ void tile_rows(dd_ctx *c, int prec, bool interface_rows, const double *x1, const
 // FP64 blocks K_II themselves when kii is set).
 // (w32: also an FP32 copy of w when not nullptr; beta: w = B y + beta w_before)
 void dense_tiles(dd_ctx *c, int prec, bool kii, const double *y, int ld, const double *base, double sign,
-                 double *w, const int *run = nullptr, float *w32 = nullptr, const double *beta = nullptr) {
+                 double *w, const int *run = nullptr, float *w32 = nullptr, const double *beta = nullptr,
+                 bool wide = false) {
   if (c->n_dit <= 0) return;
   const dim3 g(c->n_dit), b(kTW * kWave);
-#define DD_DT(MT, NCB, BLK)                                                                                \
-  hipLaunchKernelGGL((k_dense_tiles<MT, NCB>), g, b, 0, c->stream, c->NI, c->d_dit, (const MT *)(BLK),   \
+#define DD_DT(MT, NCB, BLK, ...)                                                                           \
+  hipLaunchKernelGGL((k_dense_tiles<MT, NCB, ##__VA_ARGS__>), g, b, 0, c->stream, c->NI, c->d_dit, (const MT *)(BLK),   \
                      c->d_toff, c->d_ioff, c->d_ni, y, ld, base, sign, w, run, w32, beta)
   if (kii || prec == DD_FP64) {
     const void *blk = kii ? (const void *)c->d_kii_t : c->op[DD_FP64].kinv_t;
     if (ld <= 16) DD_DT(double, 1, blk);
     else if (ld <= 32) DD_DT(double, 2, blk);
     else DD_DT(double, 4, blk);
+  } else if (wide) {
+    const void *blk = c->op[DD_MIXED].kinv_t;
+    if (ld <= 16) DD_DT(float, 1, blk, true);
+    else if (ld <= 32) DD_DT(float, 2, blk, true);
+    else DD_DT(float, 4, blk, true);
   } else {
     const void *blk = c->op[DD_MIXED].kinv_t;
     if (ld <= 16) DD_DT(float, 1, blk);
@@ -1280,6 +1291,36 @@ bool use_tiles(const dd_ctx *c, int sched, int ld, int apply, int launch) {
          launch != DD_LAUNCH_PERSISTENT && c->NI > 0 && c->n_gamma > 0;
 }
 
+// Whether a mixed solve runs the four-launch iteration with FP32 gathers on the
+// units (schur_units), as mixed sessions of the batch API with gather32 do.
+bool units32(const dd_ctx *c, int prec, int sched, int ld, int apply, int launch) {
+  return prec == DD_MIXED && (sched & 2) && c->direction_kernel && c->tiles && c->n_gamma > 0 &&
+         !((sched & 1) && !c->classic_cg) && apply != DD_APPLY_TRSM && launch != DD_LAUNCH_PERSISTENT &&
+         !use_tiles(c, sched, ld, apply, launch);
+}
+
+// S p of the four-launch iteration with FP32 gathers (direction p kept in memory,
+// FP32 copies of p and w beside them) on the units, where the context has them:
+// y = K_IG p, w = K_II^{-1} y, q = K_GG p - K_GI w and the p^T q group sums.  FP32
+// data and gathers, FP64 products and sums, as the CSR rows form them, at every
+// width (a column's result does not depend on the batch), which no width loses by
+// (one column: 2.35 ms on the CSR rows and 2.27 ms on the units for the constant
+// kernel at h = 1/96, 8.6 and 7.3 ms for peridynamics at h = 1/120).  16 columns of
+// the constant kernel: 6.23 ms a session on the CSR rows, 3.38 ms on the units,
+// with the FP64 residuals from them too.
+void schur_units(dd_ctx *c, const double *p, int ld) {
+  Work &w = c->w;
+  {
+    PhaseTimer t(c, DD_PHASE_KIG);
+    tile_rows<false>(c, DD_MIXED, false, p, nullptr, ld, nullptr, 1.0, 0.0, w.yI, nullptr, w.p32, nullptr, true);
+  }
+  {
+    PhaseTimer t(c, DD_PHASE_INTERIOR);
+    dense_tiles(c, DD_MIXED, false, w.yI, ld, nullptr, 1.0, w.wI, nullptr, w.w32, nullptr, true);
+  }
+  tile_rows<true>(c, DD_MIXED, true, p, w.wI, ld, nullptr, 1.0, -1.0, w.qG, nullptr, w.p32, w.w32, true);
+}
+
 // One substructuring solve on DD-layout data:
 //   g = bG - K_GI K_II^{-1} bI;  CG on S x = g until ||r_c||^2 <= stop2[c];
 //   uI = K_II^{-1} (bI - K_IG x);  uG = x.
@@ -1424,6 +1465,8 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
       tile_direction(c, prec, !replace, ld, uG, pA_, nact_dst, p32, z32, o.replace_drop * o.replace_drop);
       HIPCHK(c, hipGetLastError());
       return DD_OK;
+    } else if (g32 && c->tiles) {
+      schur_units(c, pA_, ld);
     } else {
       {
         PhaseTimer t(c, DD_PHASE_KIG);
@@ -2456,9 +2499,13 @@ dd_status dd_batch_step(dd_ctx *c, int32_t iters, int32_t *state_host) {
     P.x32 = w.p32;
     const unsigned gd = std::min(4096u, grid_for((size_t)c->n_gamma * L, kBlock));
     for (int it = 0; it < iters; ++it) {
-      kig_apply(c, prec, P, L, nullptr, 1.0, w.yI);
-      interior_solve(c, prec, DD_APPLY_INV, w.yI, w.wI, L);          // also w in FP32
-      gamma_apply(c, prec, P, w.wI, L, nullptr, 1.0, -1.0, w.qG, 1, nullptr);
+      if (c->tiles) {
+        schur_units(c, w.pG, L);
+      } else {
+        kig_apply(c, prec, P, L, nullptr, 1.0, w.yI);
+        interior_solve(c, prec, DD_APPLY_INV, w.yI, w.wI, L);        // also w in FP32
+        gamma_apply(c, prec, P, w.wI, L, nullptr, 1.0, -1.0, w.qG, 1, nullptr);
+      }
       launch_update(c, 1, L, kMaxLd, op.dinv, w.dG, w.rG, w.zG, w.pG, w.qG, B.o.precond, nullptr, 0,
                     nullptr, c->gamma_parts);
       hipLaunchKernelGGL(k_cg_direction, dim3(gd), dim3(kBlock), 0, c->stream, c->n_gamma, L, w.zG,
@@ -2518,7 +2565,7 @@ dd_status dd_batch_step(dd_ctx *c, int32_t iters, int32_t *state_host) {
         }
     } else {
       // FP64 residual of the finished columns; refine, finish or fall back
-      full_residual(c, w.bI, w.bG, w.uI, w.uG, w.yI, w.qG, L);
+      full_residual(c, w.bI, w.bG, w.uI, w.uG, w.yI, w.qG, L, B.g32 && c->tiles);
       TRY(dd_norm2(c, L, w.yI, w.qG, w.rnrm2));
       std::vector<double> rn(kMaxLd);
       HIPCHK(c, hipMemcpyAsync(rn.data(), w.rnrm2, kMaxLd * 8, hipMemcpyDeviceToHost, c->stream));
@@ -2681,6 +2728,7 @@ dd_status dd_solve(dd_ctx *c, dd_precision prec, const double *b_dev, double *u_
               use_cg3};
   if (c->force_direct >= 0) direct = c->force_direct != 0;
   const bool tl = use_tiles(c, co.cg3, L, co.apply, co.launch);
+  const bool tres = tl || units32(c, prec, co.cg3, L, co.apply, co.launch);     // residuals from the units
   co.direct = direct && !tl && !(co.cg3 & 2) && co.apply == DD_APPLY_INV && !c->direction_kernel;
   // residual replacement in the mixed solve (tiled path, FP64 operators formed)
   if (prec == DD_MIXED && o.reliable != 0) co.reliable = o.reliable < 0 ? kReplacePeriod : o.reliable;
@@ -2727,7 +2775,7 @@ dd_status dd_solve(dd_ctx *c, dd_precision prec, const double *b_dev, double *u_
     dd_status s = core_solve(c, DD_FP64, w.bI, w.bG, w.uI, w.uG, L, nrhs, co);
     if (s != DD_OK) return s;
     if (o.verify) {
-      full_residual(c, w.bI, w.bG, w.uI, w.uG, w.tI, w.tG, L, tl);
+      full_residual(c, w.bI, w.bG, w.uI, w.uG, w.tI, w.tG, L, tres);
       norm2(w.tI, w.tG, w.rnrm2, 0.0, nullptr);
     }
     scatter();
@@ -2760,7 +2808,7 @@ dd_status dd_solve(dd_ctx *c, dd_precision prec, const double *b_dev, double *u_
     std::vector<int> stall(kMaxLd, 0), done(kMaxLd, 0), need_fb(kMaxLd, 0), undo(kMaxLd, 0);
     for (int j = nrhs; j < kMaxLd; ++j) done[j] = 1;
     for (int step = 1;; ++step) {
-      full_residual(c, w.bI, w.bG, w.uI, w.uG, w.tI, w.tG, L, tl);
+      full_residual(c, w.bI, w.bG, w.uI, w.uG, w.tI, w.tG, L, tres);
       norm2(w.tI, w.tG, w.rnrm2, 0.0, nullptr);
       TRY(fetch_state(c, &h, false));     // inner iterations, ||b||, ||r||: one wait per step
       bool any = false, undo_any = false;
@@ -2805,7 +2853,7 @@ dd_status dd_solve(dd_ctx *c, dd_precision prec, const double *b_dev, double *u_
         hipLaunchKernelGGL(k_undo2_masked, dim3(std::min(4096u, grid_for(nIe + nGe, 256))), dim3(256), 0,
                            c->stream, nIe, nGe, L, w.dI, w.dG, w.uI, w.uG, dm, step == 1 ? 1 : 0);
         HIPCHK(c, hipGetLastError());
-        full_residual(c, w.bI, w.bG, w.uI, w.uG, w.tI, w.tG, L, tl);
+        full_residual(c, w.bI, w.bG, w.uI, w.uG, w.tI, w.tG, L, tres);
       }
       if (!any) break;
       for (int j = nrhs; j < kMaxLd; ++j) { mask[j] = 0; st2[j] = 0.0; }
@@ -2836,7 +2884,7 @@ dd_status dd_solve(dd_ctx *c, dd_precision prec, const double *b_dev, double *u_
       dd_status s = core_solve(c, DD_FP64, w.tI, w.tG, w.dI, w.dG, L, nrhs, co);
       if (s != DD_OK) return s;
       axpy(c->d_solve_mask);
-      full_residual(c, w.bI, w.bG, w.uI, w.uG, w.tI, w.tG, L, tl);
+      full_residual(c, w.bI, w.bG, w.uI, w.uG, w.tI, w.tG, L, tres);
       norm2(w.tI, w.tG, w.rnrm2, 0.0, nullptr);
       TRY(fetch_state(c, &h));
       for (int j = 0; j < nrhs; ++j) {

@@ -172,12 +172,13 @@ __device__ __forceinline__ void unit_a(const float *unit, int lane, float (&a)[4
 // steps accumulate 8 products per output element in FP32, and these sums are
 // added to the FP64 accumulators, so FP32 rounding enters only within them
 // (rows are then in the FP32 instruction's order: row 4 (l / 16) + r of lane l,
-// register r).  A pass of the loop runs unit j while the
+// register r).  WIDE: FP32 units and vector rows are widened and run on the FP64
+// instruction (every product and sum in FP64).  A pass of the loop runs unit j while the
 // operands of units j + 1 .. j + D - 1 and the column lists of the D after them
 // are in flight.  Scheduling barriers keep every group of loads in program
 // order, so that the instructions of one buffer wait only for that buffer's
 // loads; the loads past a wave's last unit are skipped.
-template <int NCB, int D, typename VT, typename XT>
+template <int NCB, int D, bool WIDE, typename VT, typename XT>
 __device__ __forceinline__ void tile_row_acc(int t0, int t1, int st, const int4 *__restrict__ tcol,
                                              const VT *__restrict__ tval, const XT *__restrict__ x, int ld,
                                              double sgn, dbl4 (&acc)[NCB]) {
@@ -199,7 +200,7 @@ __device__ __forceinline__ void tile_row_acc(int t0, int t1, int st, const int4 
     slice_row<NCB>(xc + (size_t)ix[d].w * ld, xs[d][3]);
   };
   auto mma = [&](int d) {
-    if constexpr (std::is_same<VT, float>::value) {
+    if constexpr (std::is_same<VT, float>::value && !WIDE) {
       const float fs = (float)sgn;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -258,9 +259,9 @@ __device__ __forceinline__ void tile_row_acc(int t0, int t1, int st, const int4 
 
 // Row of a 16-row block held in accumulator register r of lane group g: the
 // FP64 instruction's order (g + 4 r) or the FP32 one's (4 g + r).
-template <typename VT>
+template <typename VT, bool WIDE>
 __device__ __forceinline__ int acc_row(int g, int r) {
-  return std::is_same<VT, float>::value ? 4 * g + r : g + 4 * r;
+  return std::is_same<VT, float>::value && !WIDE ? 4 * g + r : g + 4 * r;
 }
 
 // Workgroup b runs on XCD b % 8 (round-robin dispatch; each XCD has its own
@@ -303,7 +304,7 @@ constexpr int kTW = 4;
 // iterating; when it reads 0 the launch does nothing (the loop's host runs a
 // few iterations ahead of the device).  x1f, x2f (FP32 units only; may be
 // nullptr): FP32 copies of x1, x2 whose rows the products load instead.
-template <typename VT, int NCB, bool DOT, int D, int TW>
+template <typename VT, int NCB, bool DOT, int D, int TW, bool WIDE>
 __device__ __forceinline__ void
 tile_rows_body(int rb, int nrows, int b, int s, int e, bool split, const int4 *__restrict__ tcol,
                const VT *__restrict__ tval, const double *__restrict__ x1, const double *__restrict__ x2, int ld,
@@ -336,8 +337,8 @@ tile_rows_body(int rb, int nrows, int b, int s, int e, bool split, const int4 *_
   // the units are dealt to the waves in turn through both parts, from another
   // wave in each row block (a wave keeps its SIMD, so the odd units spread)
   const int w1 = (wv + rb) & (TW - 1), w2 = (w1 - (s - b)) & (TW - 1);
-  auto part1 = [&](auto x) { tile_row_acc<NCB, D>(b + w1, s, TW, tcol, tval, x, ld, 1.0, acc); };
-  auto part2 = [&](auto x) { tile_row_acc<NCB, D>(s + w2, e, TW, tcol, tval, x, ld, sg2, acc); };
+  auto part1 = [&](auto x) { tile_row_acc<NCB, D, WIDE>(b + w1, s, TW, tcol, tval, x, ld, 1.0, acc); };
+  auto part2 = [&](auto x) { tile_row_acc<NCB, D, WIDE>(s + w2, e, TW, tcol, tval, x, ld, sg2, acc); };
   if constexpr (std::is_same<VT, float>::value) {
     if (c1 != 0.0) x1f ? part1(x1f) : part1(x1);
     if (split && c2 != 0.0) x2f ? part2(x2f) : part2(x2);
@@ -352,7 +353,7 @@ tile_rows_body(int rb, int nrows, int b, int s, int e, bool split, const int4 *_
     const int col = NCB * l16 + q;
 #pragma unroll
     for (int r = 0; r < 4; ++r)                  // row of the block held in register r
-      if (col < ld) part[(wv * kT + acc_row<VT>(g, r)) * ld + col] = cf * acc[q][r];
+      if (col < ld) part[(wv * kT + acc_row<VT, WIDE>(g, r)) * ld + col] = cf * acc[q][r];
   }
   __syncthreads();
   double fin[NF], vo[NF];
@@ -429,7 +430,7 @@ tile_rows_body(int rb, int nrows, int b, int s, int e, bool split, const int4 *_
   if (threadIdx.x == 0) reset_counter(cnt);
 }
 
-template <typename VT, int NCB, bool DOT, int D, int TW>
+template <typename VT, int NCB, bool DOT, int D, int TW, bool WIDE>
 __global__ void __launch_bounds__(TW * kWave, kMfmaWaves)
 k_tile_rows(int nrb, int nrows, const int *__restrict__ ptr, const int *__restrict__ split,
             const int4 *__restrict__ tcol, const VT *__restrict__ tval, const double *__restrict__ x1,
@@ -440,7 +441,7 @@ k_tile_rows(int nrb, int nrows, const int *__restrict__ ptr, const int *__restri
   // (loaded beside the flag, not after it: one memory round trip less)
   const int b = ptr[rb], e = ptr[rb + 1], s = split ? split[rb] : e;
   if (run && *run == 0) return;                  // every column of the CG loop has stopped
-  tile_rows_body<VT, NCB, DOT, D, TW>(rb, nrows, b, s, e, split != nullptr, tcol, tval, x1, x2, ld, base, c1, c2,
+  tile_rows_body<VT, NCB, DOT, D, TW, WIDE>(rb, nrows, b, s, e, split != nullptr, tcol, tval, x1, x2, ld, base, c1, c2,
                                       out, red, nrb, x1f, x2f, grouped != 0);
 }
 
@@ -627,7 +628,7 @@ k_tile_direction(int nrows, int ld, const double *__restrict__ z, double *__rest
     const int rb = xcd_item((int)blockIdx.x - 1, nrb);
     const int b = ptr[rb], e = ptr[rb + 1];
     if (none) return;
-    tile_rows_body<VT, NCB, false, 2, 4>(rb, nI, b, e, e, false, tcol, tval, z, nullptr, ld, nullptr, 1.0, 0.0, u,
+    tile_rows_body<VT, NCB, false, 2, 4, false>(rb, nI, b, e, e, false, tcol, tval, z, nullptr, ld, nullptr, 1.0, 0.0, u,
                                          red, nrb, z32, nullptr, false);
     return;
   }
@@ -740,7 +741,8 @@ k_tile_direction(int nrows, int ld, const double *__restrict__ z, double *__rest
 // row, zero padded).  Wave w applies the tiles J = w, w + kTW, ... to the
 // 16-row slices of y; the wave sums are added in wave order.  FP64 blocks:
 // v_mfma_f64_16x16x4f64; FP32 blocks (mixed path): v_mfma_f32_16x16x4f32 with
-// FP32 operands and accumulation, the wave sums added in FP64.  beta (may be
+// FP32 operands and accumulation, the wave sums added in FP64; WIDE: FP32 blocks
+// widened, on the FP64 instruction with FP64 y and sums.  beta (may be
 // nullptr): w += beta w_before per column (the CG's recurrence, k_tile_direction).
 template <typename MT> struct DenseAcc;
 template <> struct DenseAcc<double> {
@@ -770,7 +772,7 @@ template <> struct TileAT<float> {
   }
 };
 
-template <typename MT, int NCB>
+template <typename MT, int NCB, bool WIDE = false>
 __global__ void __launch_bounds__(kTW * kWave, kMfmaWaves)
 k_dense_tiles(int nall, const int2 *__restrict__ items, const MT *__restrict__ packed,
               const long long *__restrict__ toff, const int *__restrict__ ioff,
@@ -800,33 +802,35 @@ k_dense_tiles(int nall, const int2 *__restrict__ items, const MT *__restrict__ p
   // y rows past the block (the next subdomain's, or the last row repeated at
   // the end of y) meet the zero padding of the packed tiles
   const double *yb = y + slice_col0<NCB>(l16, ld);
-  typedef typename DenseAcc<MT>::acc_t acc_t;
+  typedef typename std::conditional<WIDE, double, MT>::type AT;
+  typedef typename DenseAcc<AT>::acc_t acc_t;
   acc_t acc[NCB];
 #pragma unroll
   for (int q = 0; q < NCB; ++q)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[q][r] = (MT)0;
-  auto load = [&](int J, MT (&a)[4], MT (&b)[4][NCB]) {
+    for (int r = 0; r < 4; ++r) acc[q][r] = (AT)0;
+  auto load = [&](int J, MT (&a)[4], AT (&b)[4][NCB]) {
     TileAT<MT>::load(A + (size_t)J * 256, lane, a);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       double v[NCB];
       slice_row<NCB>(yb + (size_t)min(i0 + J * kT + 4 * s + g, nall - 1) * ld, v);
 #pragma unroll
-      for (int q = 0; q < NCB; ++q) b[s][q] = (MT)v[q];
+      for (int q = 0; q < NCB; ++q) b[s][q] = (AT)v[q];
     }
   };
-  auto mma = [&](const MT (&a)[4], const MT (&b)[4][NCB]) {
+  auto mma = [&](const MT (&a)[4], const AT (&b)[4][NCB]) {
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int q = 0; q < NCB; ++q) acc[q] = mfma16x16x4(a[s], b[s][q], acc[q]);
+      for (int q = 0; q < NCB; ++q) acc[q] = mfma16x16x4((AT)a[s], b[s][q], acc[q]);
   };
   // tiles J = wv, wv + kTW, ...: two register buffers in flight, each group of
   // loads kept in program order (see tile_row_acc)
   const int cnt = wv < nt ? (nt - wv + kTW - 1) / kTW : 0;
   if (cnt > 0) {
-    MT a0[4], b0[4][NCB], a1[4], b1[4][NCB];
+    MT a0[4], a1[4];
+    AT b0[4][NCB], b1[4][NCB];
     load(wv, a0, b0);
     __builtin_amdgcn_sched_barrier(0);
     load(wv + kTW * min(1, cnt - 1), a1, b1);
@@ -848,7 +852,7 @@ k_dense_tiles(int nall, const int2 *__restrict__ items, const MT *__restrict__ p
     const int c = NCB * l16 + q;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (c < ld) part[(wv * kT + DenseAcc<MT>::row(g, r)) * ld + c] = (double)acc[q][r];
+      if (c < ld) part[(wv * kT + DenseAcc<AT>::row(g, r)) * ld + c] = (double)acc[q][r];
   }
   __syncthreads();
   const int nel = kT * ld;

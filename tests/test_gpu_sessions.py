@@ -1,4 +1,6 @@
-"""GPU test of batch sessions: a session after one whose iterate became NaN."""
+"""GPU tests of batch sessions: a session after one whose iterate became NaN, and
+mixed sessions with FP32 gathers on contexts with units (max_nrhs >= 8) at block
+edges and column counts on both sides of each layout width."""
 import numpy as np
 import pytest
 
@@ -46,3 +48,27 @@ def test_session_after_nan(prec):
         out.append(session(dd, s, b, prec, opts, 1)[0])
         s.close()
     assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("n_gamma,sizes", [(1, (1, 2)), (16, (5, 1)), (17, (33, 16, 1)), (100, (7, 20, 31))])
+def test_mixed_sessions_on_units(n_gamma, sizes):
+    """1 to 33 columns of a mixed session with FP32 gathers: the refined solution
+    of systems with condition numbers below 100 (tolerance 1e-13: error below
+    1e-8 with a wide margin), and a column's bits independent of the others."""
+    dd = _dd()
+    A, p = system(n_gamma, sizes, seed=7)
+    s = dd.Solver(p, max_nrhs=64)
+    s.factor(dd.DD_MIXED)
+    opts = dd.dd_default_opts(tol=1e-13, gather32=1)
+    b = np.random.default_rng(8).uniform(-1, 1, (33, len(A)))
+    ref = np.linalg.solve(A, b.T).T
+    one = None
+    for m in (1, 2, 7, 9, 16, 17, 33):
+        print(f"case mixed session on units n_gamma={n_gamma} columns={m}", flush=True)
+        u, info = session(dd, s, torch.from_numpy(b[:m].copy()).cuda(), dd.DD_MIXED, opts, 64)
+        assert all(i["converged"] for i in info)
+        err = np.linalg.norm(u - ref[:m], axis=1) / np.linalg.norm(ref[:m], axis=1)
+        assert err.max() <= 1e-8, err
+        one = u[0] if one is None else one
+        assert np.array_equal(u[0], one)
+    s.close()
