@@ -682,14 +682,13 @@ template <typename VT, int NCB, bool DOT, bool WIDE>
 void launch_tile_rows_t(dd_ctx *c, bool interface_rows, const VT *val, const double *x1,
                         const double *x2, int ld, const double *base, double c1, double c2,
                         double *out, const int *run, const float *x1f, const float *x2f) {
-  // (WIDE: the step behind these products is k_cg_update, which reads group sums)
   const int nrb = interface_rows ? c->t_nrbG : c->t_nrbI;
   const int nrows = interface_rows ? c->n_gamma : c->NI;
   if (nrb <= 0) return;
   const int *ptr = interface_rows ? c->d_tG_ptr : c->d_tI_ptr;
   const int *split = interface_rows ? c->d_tG_split : nullptr;
   const int4 *col = (const int4 *)(interface_rows ? c->d_tG_col : c->d_tI_col);
-  const int grouped = WIDE || dot_grouped(nrb);
+  const int grouped = WIDE || dot_grouped(nrb);       // (WIDE: k_cg_update reads group sums)
   if (DOT) c->gamma_parts = grouped ? (nrb + kPGroup - 1) / kPGroup : nrb;      // sums of p^T q
   hipEvent_t e0 = nullptr, e1 = nullptr;
   constexpr int kDepth = 2, kWaves = 4;        // units in flight per wave, waves per row block
@@ -1291,23 +1290,25 @@ bool use_tiles(const dd_ctx *c, int sched, int ld, int apply, int launch) {
          launch != DD_LAUNCH_PERSISTENT && c->NI > 0 && c->n_gamma > 0;
 }
 
-// Whether a mixed solve runs the four-launch iteration with FP32 gathers on the
-// units (schur_units), as mixed sessions of the batch API with gather32 do.
+// Whether a solve runs the four-launch iteration with FP32 gathers on the units
+// (schur_units), as mixed sessions of the batch API with gather32 do in contexts
+// that have units: at every width, since a column's result must not depend on the
+// batch.  One column in a context of 16 takes 2.35 ms on the CSR rows and 2.31 ms on
+// the units for the constant kernel at h = 1/96, 4.15 and 4.2 ms for the fractional
+// one at h = 1/72, 8.6 and 7.4 ms for peridynamics at h = 1/120; 16 columns 6.2 and
+// 3.0 ms, 10.5 and 5.4 ms, 31.7 and 11.6 ms.  (Without FP32 gathers it would: the CSR rows form the direction as they
+// gather it, the units need the direction launch.  One FP64 column, constant
+// kernel: 1.33 and 1.72 ms.)
 bool units32(const dd_ctx *c, int prec, int sched, int ld, int apply, int launch) {
-  return prec == DD_MIXED && (sched & 2) && c->direction_kernel && c->tiles && c->n_gamma > 0 &&
+  return prec == DD_MIXED && (sched & 2) && c->direction_kernel && c->tiles && c->NI > 0 && c->n_gamma > 0 &&
          !((sched & 1) && !c->classic_cg) && apply != DD_APPLY_TRSM && launch != DD_LAUNCH_PERSISTENT &&
          !use_tiles(c, sched, ld, apply, launch);
 }
 
-// S p of the four-launch iteration with FP32 gathers (direction p kept in memory,
-// FP32 copies of p and w beside them) on the units, where the context has them:
-// y = K_IG p, w = K_II^{-1} y, q = K_GG p - K_GI w and the p^T q group sums.  FP32
-// data and gathers, FP64 products and sums, as the CSR rows form them, at every
-// width (a column's result does not depend on the batch), which no width loses by
-// (one column: 2.35 ms on the CSR rows and 2.27 ms on the units for the constant
-// kernel at h = 1/96, 8.6 and 7.3 ms for peridynamics at h = 1/120).  16 columns of
-// the constant kernel: 6.23 ms a session on the CSR rows, 3.38 ms on the units,
-// with the FP64 residuals from them too.
+// Products of that iteration: FP32 operators, products and sums in FP64 as the CSR
+// rows form them.
+// S p: y = K_IG p, w = K_II^{-1} y, q = K_GG p - K_GI w and the p^T q group sums
+// (p and w gathered from their FP32 copies).
 void schur_units(dd_ctx *c, const double *p, int ld) {
   Work &w = c->w;
   {
@@ -1319,6 +1320,18 @@ void schur_units(dd_ctx *c, const double *p, int ld) {
     dense_tiles(c, DD_MIXED, false, w.yI, ld, nullptr, 1.0, w.wI, nullptr, w.w32, nullptr, true);
   }
   tile_rows<true>(c, DD_MIXED, true, p, w.wI, ld, nullptr, 1.0, -1.0, w.qG, nullptr, w.p32, w.w32, true);
+}
+
+// Condensation out = bG - K_GI K_II^{-1} bI and back substitution uI = K_II^{-1}
+// (bI - K_IG uG) around it.
+void condense_units(dd_ctx *c, const double *bI, const double *bG, double *out, int ld) {
+  dense_tiles(c, DD_MIXED, false, bI, ld, nullptr, 1.0, c->w.wI, nullptr, nullptr, nullptr, true);
+  tile_rows<false>(c, DD_MIXED, true, nullptr, c->w.wI, ld, bG, 0.0, -1.0, out, nullptr, nullptr, nullptr, true);
+}
+
+void back_units(dd_ctx *c, const double *bI, const double *uG, double *uI, int ld) {
+  tile_rows<false>(c, DD_MIXED, false, uG, nullptr, ld, bI, -1.0, 0.0, c->w.yI, nullptr, nullptr, nullptr, true);
+  dense_tiles(c, DD_MIXED, false, c->w.yI, ld, nullptr, 1.0, uI, nullptr, nullptr, nullptr, true);
 }
 
 // One substructuring solve on DD-layout data:
@@ -1342,8 +1355,11 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
                    c->op[DD_FP64].kinv_t && c->n_gamma > 0) ? o.reliable : 0;
   const int cprec = rel ? DD_FP64 : prec;    // operators of condensation and back substitution
   double *gG = w.r2G;                        // condensed right-hand side g (unused by the tiled loop)
+  const bool u32 = units32(c, prec, o.cg3, ld, o.apply, o.launch);
   // condensation (eq. subForcing summed over subdomains): r = bG - K_GI K_II^{-1} bI
-  if (tl) {
+  if (u32) {
+    condense_units(c, bI, bG, w.rG, ld);
+  } else if (tl) {
     dense_tiles(c, cprec, false, bI, ld, nullptr, 1.0, w.wI);
     tile_rows<false>(c, cprec, true, nullptr, w.wI, ld, bG, 0.0, -1.0, w.rG);
     if (rel)
@@ -1465,7 +1481,7 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
       tile_direction(c, prec, !replace, ld, uG, pA_, nact_dst, p32, z32, o.replace_drop * o.replace_drop);
       HIPCHK(c, hipGetLastError());
       return DD_OK;
-    } else if (g32 && c->tiles) {
+    } else if (u32) {
       schur_units(c, pA_, ld);
     } else {
       {
@@ -1613,7 +1629,9 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
   }
   c->g32 = Gather32{};
   // back substitution (eq. backwardSubstitution): uI = K_II^{-1} (bI - K_IG uG)
-  if (tl) {
+  if (u32) {
+    back_units(c, bI, uG, uI, ld);
+  } else if (tl) {
     tile_rows<false>(c, cprec, false, uG, nullptr, ld, bI, -1.0, 0.0, w.yI);
     dense_tiles(c, cprec, false, w.yI, ld, nullptr, 1.0, uI);
   } else {
@@ -2389,8 +2407,13 @@ dd_status batch_start_cg(dd_ctx *c, const int *mask, const double *rI, const dou
   if (rI != w.tI)
     hipLaunchKernelGGL(k_cols_update, dim3(grid1d((size_t)c->NI * ld)), dim3(256), 0, c->stream,
                        (size_t)c->NI * ld, ld, 0.0, rI, w.tI, B.d_mask);
-  interior_solve(c, B.prec, DD_APPLY_INV, w.tI, w.wI, ld);
-  gamma_apply(c, B.prec, plain(nullptr), w.wI, ld, rG, 0.0, -1.0, w.qG);
+  const bool un = B.g32 && c->tiles;       // on the units (units32)
+  if (un) {
+    condense_units(c, w.tI, rG, w.qG, ld);
+  } else {
+    interior_solve(c, B.prec, DD_APPLY_INV, w.tI, w.wI, ld);
+    gamma_apply(c, B.prec, plain(nullptr), w.wI, ld, rG, 0.0, -1.0, w.qG);
+  }
   std::vector<double> st2(B.stop2, B.stop2 + kMaxLd);
   HIPCHK(c, hipMemcpyAsync(c->st.stop2, st2.data(), kMaxLd * 8, hipMemcpyHostToDevice, c->stream));
   // first direction: z itself when the direction kernel keeps it (FP32
@@ -2488,6 +2511,7 @@ dd_status dd_batch_step(dd_ctx *c, int32_t iters, int32_t *state_host) {
   const int prec = B.prec;
   bool any = false;
   for (int j = 0; j < kMaxLd; ++j) any |= B.state[j] == DD_SLOT_RUNNING;
+  const bool un = B.g32 && c->tiles;       // on the units (units32)
   if (any && iters > 0 && c->n_gamma > 0 && B.g32) {
     // direction kept in pG; its FP32 copy is refreshed here because the
     // admissions and retirements in between change the column stride
@@ -2499,7 +2523,7 @@ dd_status dd_batch_step(dd_ctx *c, int32_t iters, int32_t *state_host) {
     P.x32 = w.p32;
     const unsigned gd = std::min(4096u, grid_for((size_t)c->n_gamma * L, kBlock));
     for (int it = 0; it < iters; ++it) {
-      if (c->tiles) {
+      if (un) {
         schur_units(c, w.pG, L);
       } else {
         kig_apply(c, prec, P, L, nullptr, 1.0, w.yI);
@@ -2544,8 +2568,12 @@ dd_status dd_batch_step(dd_ctx *c, int32_t iters, int32_t *state_host) {
   }
   if (anyfin) {
     TRY(batch_mask(c, fin.data()));
-    kig_apply(c, prec, plain(w.dG), L, w.tI, -1.0, w.yI);
-    interior_solve(c, prec, DD_APPLY_INV, w.yI, w.dI, L);
+    if (un) {
+      back_units(c, w.tI, w.dG, w.dI, L);
+    } else {
+      kig_apply(c, prec, plain(w.dG), L, w.tI, -1.0, w.yI);
+      interior_solve(c, prec, DD_APPLY_INV, w.yI, w.dI, L);
+    }
     hipLaunchKernelGGL(k_axpy_masked, dim3(grid1d((size_t)c->NI * L)), dim3(256), 0, c->stream,
                        (size_t)c->NI * L, L, w.dI, w.uI, B.d_mask);
     hipLaunchKernelGGL(k_axpy_masked, dim3(grid1d((size_t)c->n_gamma * L)), dim3(256), 0, c->stream,
@@ -2565,7 +2593,7 @@ dd_status dd_batch_step(dd_ctx *c, int32_t iters, int32_t *state_host) {
         }
     } else {
       // FP64 residual of the finished columns; refine, finish or fall back
-      full_residual(c, w.bI, w.bG, w.uI, w.uG, w.yI, w.qG, L, B.g32 && c->tiles);
+      full_residual(c, w.bI, w.bG, w.uI, w.uG, w.yI, w.qG, L, un);
       TRY(dd_norm2(c, L, w.yI, w.qG, w.rnrm2));
       std::vector<double> rn(kMaxLd);
       HIPCHK(c, hipMemcpyAsync(rn.data(), w.rnrm2, kMaxLd * 8, hipMemcpyDeviceToHost, c->stream));
@@ -2728,8 +2756,8 @@ dd_status dd_solve(dd_ctx *c, dd_precision prec, const double *b_dev, double *u_
               use_cg3};
   if (c->force_direct >= 0) direct = c->force_direct != 0;
   const bool tl = use_tiles(c, co.cg3, L, co.apply, co.launch);
-  const bool tres = tl || units32(c, prec, co.cg3, L, co.apply, co.launch);     // residuals from the units
   co.direct = direct && !tl && !(co.cg3 & 2) && co.apply == DD_APPLY_INV && !c->direction_kernel;
+  const bool tres = tl || units32(c, prec, co.cg3, L, co.apply, co.launch);     // residuals from the units
   // residual replacement in the mixed solve (tiled path, FP64 operators formed)
   if (prec == DD_MIXED && o.reliable != 0) co.reliable = o.reliable < 0 ? kReplacePeriod : o.reliable;
   co.replace_drop = itol_requested > 0.0 ? itol_requested : (tuned_drop > 0.0 ? tuned_drop : kReplaceDrop);

@@ -1,5 +1,5 @@
 """GPU tests of batch sessions: a session after one whose iterate became NaN, and
-mixed sessions with FP32 gathers on contexts with units (max_nrhs >= 8) at block
+sessions on contexts with units (max_nrhs >= 8) at block
 edges and column counts on both sides of each layout width."""
 import numpy as np
 import pytest
@@ -51,24 +51,26 @@ def test_session_after_nan(prec):
 
 
 @pytest.mark.parametrize("n_gamma,sizes", [(1, (1, 2)), (16, (5, 1)), (17, (33, 16, 1)), (100, (7, 20, 31))])
-def test_mixed_sessions_on_units(n_gamma, sizes):
-    """1 to 33 columns of a mixed session with FP32 gathers: the refined solution
-    of systems with condition numbers below 100 (tolerance 1e-13: error below
-    1e-8 with a wide margin), and a column's bits independent of the others."""
+@pytest.mark.parametrize("prec,gather32", [(0, -1), (1, 0), (1, 1)])
+def test_sessions_on_units(n_gamma, sizes, prec, gather32):
+    """1 to 33 columns of a session: the solution of systems with condition
+    numbers below 100 (tolerance 1e-13: error below 1e-10 in FP64 and 1e-8 in
+    mixed precision with a wide margin), and a column's bits independent of the
+    others."""
     dd = _dd()
     A, p = system(n_gamma, sizes, seed=7)
     s = dd.Solver(p, max_nrhs=64)
-    s.factor(dd.DD_MIXED)
-    opts = dd.dd_default_opts(tol=1e-13, gather32=1)
+    s.factor(prec)
+    opts = dd.dd_default_opts(tol=1e-13, gather32=gather32)
     b = np.random.default_rng(8).uniform(-1, 1, (33, len(A)))
     ref = np.linalg.solve(A, b.T).T
     one = None
     for m in (1, 2, 7, 9, 16, 17, 33):
-        print(f"case mixed session on units n_gamma={n_gamma} columns={m}", flush=True)
-        u, info = session(dd, s, torch.from_numpy(b[:m].copy()).cuda(), dd.DD_MIXED, opts, 64)
+        print(f"case session on units n_gamma={n_gamma} prec={prec} gather32={gather32} columns={m}", flush=True)
+        u, info = session(dd, s, torch.from_numpy(b[:m].copy()).cuda(), prec, opts, 64)
         assert all(i["converged"] for i in info)
         err = np.linalg.norm(u - ref[:m], axis=1) / np.linalg.norm(ref[:m], axis=1)
-        assert err.max() <= 1e-8, err
+        assert err.max() <= (1e-8 if prec else 1e-10), err
         one = u[0] if one is None else one
         assert np.array_equal(u[0], one)
     s.close()
