@@ -94,6 +94,180 @@ __global__ void k_dot_fin(int nparts, int ld, const double *__restrict__ part, d
   out[c] = s;
 }
 
+// State of the projected PCG over the multipliers, kept on the device between
+// launches: its step lengths never go through the host.
+struct FetiState {
+  double coef[kMaxLd];                           // beta or alpha of the step under way
+  double wy[kMaxLd], wy_old[kMaxLd], w0[kMaxLd];
+  int active[kMaxLd], its[kMaxLd];
+  int broken;
+  unsigned count;                                // workgroups of the dot under way
+};
+// What the host reads of it (pinned), written once per iteration.
+struct FetiHost {
+  int any, broken;
+  int active[kMaxLd], its[kMaxLd];
+};
+enum { kFetiStart, kFetiBeta, kFetiAlpha, kFetiCheck };
+
+// Column dots as k_dot_part's, finished by the last workgroup, which also does what
+// the iteration does with them:
+//   kFetiStart  w.w: ||w_0||, the columns that iterate
+//   kFetiBeta   w.y: beta = (w.y) / (w.y)_old (0 in the first iteration)
+//   kFetiAlpha  p.q: alpha = (w.y) / (p.q); p.q <= 0 is noted as a breakdown
+//   kFetiCheck  w.w: the stopping test of iteration it, and the state to the host
+// A latency chain (partial store, count, sums, scalars), 4.3 us; one launch and no
+// host in it.  Two launches (2.6 + 4.1 us), a copy and a host wait per dot: with
+// them a solve of the fixed-ratio ladder at h = 1/64 took 4.1 ms, now 2.4 ms
+// (22 iterations; k_feti_deflate included).
+__global__ void __launch_bounds__(kBlock)
+k_feti_dot(int mode, int it, double tol, int n, int ld, int nrhs, const double *__restrict__ x,
+           const double *__restrict__ y, double *__restrict__ part, FetiState *__restrict__ st,
+           FetiHost *__restrict__ host) {
+  __shared__ double lds[kRowsE * kMaxLd];
+  __shared__ int sact[kMaxLd];
+  __shared__ int lflag;
+  const int r0 = blockIdx.x * kRowsE;
+  for (int e = threadIdx.x; e < kRowsE * ld; e += kBlock) {
+    const int lr = e / ld, c = e - lr * ld, r = r0 + lr;
+    lds[e] = r < n ? x[(size_t)r * ld + c] * y[(size_t)r * ld + c] : 0.0;
+  }
+  __syncthreads();
+  for (int c = wave_id(); c < ld; c += kWavesPerBlock) {
+    const double s = chunk64_sum(lds, ld, c);
+    if (lane_id() == 0)
+      __hip_atomic_store(part + (size_t)blockIdx.x * ld + c, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // the partial stores complete before the count
+  if (!last_block(&st->count, &lflag)) return;
+  for (int c = wave_id(); c < ld; c += kWavesPerBlock) {
+    const double s = partials_sum(part, gridDim.x, ld, c);
+    if (lane_id() != 0) continue;
+    const int act = st->active[c];
+    if (mode == kFetiStart) {
+      const double n0 = sqrt(s);
+      st->w0[c] = n0;
+      sact[c] = c < nrhs && n0 > 0.0;
+    } else if (mode == kFetiBeta) {
+      st->coef[c] = (it == 0 || !act) ? 0.0 : s / st->wy_old[c];
+      st->wy[c] = s;
+    } else if (mode == kFetiAlpha) {
+      const bool bad = act && !(s > 0.0);
+      if (bad) st->broken = 1;
+      st->coef[c] = act && !bad ? st->wy[c] / s : 0.0;
+      st->wy_old[c] = st->wy[c];
+    } else {
+      sact[c] = act && !(sqrt(s) <= tol * st->w0[c]);
+      if (act) st->its[c] = it;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) reset_counter(&st->count);
+  if (mode != kFetiStart && mode != kFetiCheck) return;
+  if ((int)threadIdx.x < ld) {
+    const int c = threadIdx.x;
+    st->active[c] = sact[c];
+    if (mode == kFetiStart) st->its[c] = 0;
+    host->active[c] = sact[c];
+    host->its[c] = mode == kFetiStart ? 0 : st->its[c];
+  }
+  if (threadIdx.x == 0) {
+    int any = 0;
+    for (int c = 0; c < ld; ++c) any |= sact[c];
+    if (mode == kFetiStart) st->broken = 0;
+    host->any = any;
+    host->broken = mode == kFetiStart ? 0 : st->broken;
+  }
+}
+
+// p = y + beta p (first: p = y), and lambda += alpha p, r -= alpha q, with the
+// device's coefficients.
+__global__ void k_feti_direction(size_t n, int ld, int first, const double *__restrict__ y,
+                                 const FetiState *__restrict__ st, double *__restrict__ p) {
+  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n * ld;
+       e += (size_t)gridDim.x * blockDim.x)
+    p[e] = first ? y[e] : fma(st->coef[e % ld], p[e], y[e]);
+}
+__global__ void k_feti_update(size_t n, int ld, const double *__restrict__ p, const double *__restrict__ q,
+                              const FetiState *__restrict__ st, double *__restrict__ lam,
+                              double *__restrict__ r) {
+  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n * ld;
+       e += (size_t)gridDim.x * blockDim.x) {
+    const double a = st->coef[e % ld];
+    lam[e] = fma(a, p[e], lam[e]);
+    r[e] = fma(-a, q[e], r[e]);
+  }
+}
+
+// out = x - Q Q^T x (out may be x): Q is block diagonal with orthonormal columns,
+// n_z (at most 8) per subdomain, so one workgroup per subdomain and 8 columns does
+// both products, 64 rows at a time, in the same order at every width.  Bound by two
+// dependent passes over the subdomain's rows: 5.4 us at h = 1/64, one column (7.6
+// with the rows read four at a time), in place of two CSR products of about 3.5 us
+// and the gap between them.
+__global__ void __launch_bounds__(512)
+k_feti_deflate(const int *__restrict__ uoff, const int *__restrict__ ng, const int *__restrict__ qptr,
+               const double *__restrict__ qval, int ld, const double *x, double *out) {
+  constexpr int MZ = 8, R = 8, NW = 512 / kWave;
+  __shared__ double part[NW][MZ][8];
+  const int k = blockIdx.x, u0 = uoff[k], n = ng[k];
+  if (n == 0) return;
+  const int c = blockIdx.y * 8 + (threadIdx.x & 7), row = threadIdx.x >> 3;
+  const int a0 = qptr[u0], nz = qptr[u0 + 1] - a0;     // (every row of a subdomain has n_z entries)
+  // the first R rows of a thread stay in registers for the second pass, their loads
+  // in flight together
+  const bool on = c < ld;
+  const double *xc = x + (size_t)u0 * ld + c;
+  double z[MZ] = {}, xr[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) xr[i] = on && row + 64 * i < n ? xc[(size_t)(row + 64 * i) * ld] : 0.0;
+#pragma unroll
+  for (int m = 0; m < MZ; ++m)
+    if (m < nz) {
+      double qr[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) qr[i] = qval[a0 + (size_t)min(row + 64 * i, n - 1) * nz + m];
+#pragma unroll
+      for (int i = 0; i < R; ++i) z[m] = fma(qr[i], xr[i], z[m]);
+    }
+  if (on)
+    for (int j = row + 64 * R; j < n; j += 64) {
+      const double v = xc[(size_t)j * ld];
+#pragma unroll
+      for (int m = 0; m < MZ; ++m)
+        if (m < nz) z[m] = fma(qval[a0 + (size_t)j * nz + m], v, z[m]);
+    }
+#pragma unroll
+  for (int m = 0; m < MZ; ++m)
+    if (m < nz) {
+      double v = z[m];
+      v += __shfl_xor(v, 8, kWave);
+      v += __shfl_xor(v, 16, kWave);
+      v += __shfl_xor(v, 32, kWave);
+      if (lane_id() < 8) part[wave_id()][m][lane_id()] = v;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < MZ; ++m) {
+    z[m] = 0.0;
+    if (m < nz)
+#pragma unroll
+      for (int w = 0; w < NW; ++w) z[m] += part[w][m][threadIdx.x & 7];
+  }
+  if (!on) return;
+  auto store = [&](int j, double xv) {
+    double v = 0.0;
+#pragma unroll
+    for (int m = 0; m < MZ; ++m)
+      if (m < nz) v = fma(qval[a0 + (size_t)j * nz + m], z[m], v);
+    out[(size_t)(u0 + j) * ld + c] = xv - v;
+  };
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+    if (row + 64 * i < n) store(row + 64 * i, xr[i]);
+  for (int j = row + 64 * R; j < n; j += 64) store(j, xc[(size_t)j * ld]);
+}
+
 // Per-column coefficients, passed by value with the launch (captured when
 // the kernel is enqueued: no host buffer that a later step could overwrite
 // before the copy runs).
@@ -199,7 +373,7 @@ struct dd_feti_ctx {
   hipStream_t stream = nullptr;
   int K = 0, NI = 0, NU = 0, nlam = 0, nc = 0, n_dof = 0, n_gamma = 0, max_nrhs = 0, ldmax = 1;
   std::vector<int> uoff;                    // offset of subdomain k's copy in U
-  DCsr B, Bt, BD, BDt, Gm, Gt, GtGi, Q, Qt, Zm, Zt;
+  DCsr B, Bt, BD, BDt, Gm, Gt, GtGi, Q, Zm, Zt;
   // S^+ blocks W_k (interface block of the pinned inverse), packed tiles
   double *W = nullptr;
   long long *d_wtoff = nullptr;
@@ -214,6 +388,9 @@ struct dd_feti_ctx {
          *d = nullptr, *tU = nullptr, *sU = nullptr, *fU = nullptr, *cz = nullptr, *cz2 = nullptr;
   double *dpart = nullptr, *dout = nullptr;
   double *h_dots = nullptr;                      // pinned
+  dd::FetiState *st = nullptr;
+  dd::FetiHost *h_st = nullptr, *h_st_dev = nullptr;     // pinned, and its device address
+  hipEvent_t ev = nullptr;                       // behind the stopping test of an iteration
   dd::ColCoef coef{};                            // coefficients of the next axpy / xpay
   bool factored = false;
   // balancing Neumann-Neumann preconditioner of the primal interface problem:
@@ -366,12 +543,23 @@ void xpay(dd_feti_ctx *f, size_t n, int ld, const double *x, double *y) {
                      f->coef, y);
 }
 
+// One dot of the multiplier PCG and what follows from it (k_feti_dot).
+void feti_dot(dd_feti_ctx *f, int mode, int it, double tol, int ld, int nrhs, const double *x, const double *y) {
+  hipLaunchKernelGGL(k_feti_dot, dim3(grid_for(f->nlam, kRowsE)), dim3(kBlock), 0, f->stream, mode, it, tol, f->nlam,
+                     ld, nrhs, x, y, f->dpart, f->st, f->h_st_dev);
+}
+
+// out = x - Q Q^T x on U (in place allowed).
+void deflate(dd_feti_ctx *f, const double *x, double *out, int ld) {
+  hipLaunchKernelGGL(k_feti_deflate, dim3(f->K, (ld + 7) / 8), dim3(512), 0, f->stream, f->d_wioff, f->d_wni,
+                     f->Q.ptr, f->Q.val, ld, x, out);
+}
+
 // S^+ x on U (out may not alias x): project off the kernels, W_k blocks, project.
 void spinv(dd_feti_ctx *f, const double *x, double *out, int ld) {
   const double *in = x;
   if (f->nc > 0) {          // t = x - Q Q^T x
-    csr_apply(f, f->Qt, x, ld, nullptr, 1.0, f->cz);
-    csr_apply(f, f->Q, f->cz, ld, x, -1.0, f->tU);
+    deflate(f, x, f->tU, ld);
     in = f->tU;
   }
   const dim3 g(f->n_wit), b(kTW * kWave);
@@ -384,8 +572,7 @@ void spinv(dd_feti_ctx *f, const double *x, double *out, int ld) {
   else DD_WT(4);
 #undef DD_WT
   if (f->nc > 0) {
-    csr_apply(f, f->Qt, out, ld, nullptr, 1.0, f->cz);
-    csr_apply(f, f->Q, f->cz, ld, out, -1.0, out);
+    deflate(f, out, out, ld);
   }
 }
 
@@ -728,7 +915,6 @@ dd_status dd_feti_setup(const dd_problem *prob, const dd_feti_sub *fs, void *hip
   if ((st = up_csr(f, Gt, f->Gt)) != DD_OK) return bail(st);
   if ((st = up_csr(f, GtGi, f->GtGi)) != DD_OK) return bail(st);
   if ((st = up_csr(f, Q, f->Q)) != DD_OK) return bail(st);
-  if ((st = up_csr(f, Q.transpose(), f->Qt)) != DD_OK) return bail(st);
   if ((st = up_csr(f, Z, f->Zm)) != DD_OK) return bail(st);
   if ((st = up_csr(f, Z.transpose(), f->Zt)) != DD_OK) return bail(st);
   {
@@ -903,11 +1089,21 @@ dd_status dd_feti_setup(const dd_problem *prob, const dd_feti_sub *fs, void *hip
   if ((st = dalloc(c, &f->cz, (size_t)std::max(1, nc) * L)) != DD_OK ||
       (st = dalloc(c, &f->cz2, (size_t)std::max(1, nc) * L)) != DD_OK ||
       (st = dalloc(c, &f->dpart, (size_t)(grid_for(std::max(std::max(f->nlam, NU), NI), kRowsE) + 1) * kMaxLd)) != DD_OK ||
-      (st = dalloc(c, &f->dout, kMaxLd)) != DD_OK)
+      (st = dalloc(c, &f->dout, kMaxLd)) != DD_OK || (st = dalloc(c, &f->st, 1)) != DD_OK)
     return bail(st);
   if (hipHostMalloc((void **)&f->h_dots, kMaxLd * sizeof(double), hipHostMallocDefault) != hipSuccess) {
     f->err = "pinned host allocation failed";
     return bail(DD_ENOMEM);
+  }
+  if (hipHostMalloc((void **)&f->h_st, sizeof(FetiHost), hipHostMallocDefault) != hipSuccess ||
+      hipHostGetDevicePointer((void **)&f->h_st_dev, f->h_st, 0) != hipSuccess) {
+    f->err = "pinned host allocation failed";
+    return bail(DD_ENOMEM);
+  }
+  if (hipEventCreateWithFlags(&f->ev, hipEventDisableTiming) != hipSuccess ||
+      hipMemsetAsync(f->st, 0, sizeof(FetiState), f->stream) != hipSuccess) {
+    f->err = "iteration state";
+    return bail(DD_EHIP);
   }
   *out = f;
   return DD_OK;
@@ -958,60 +1154,46 @@ dd_status dd_feti_solve(dd_feti_ctx *f, const double *b_dev, double *u_dev, int3
   // r = d - F lambda_0, w = P r
   fapply(f, f->lam, f->q, L);
   FHIP(hipMemcpyAsync(f->r, f->d, nl * L * sizeof(double), hipMemcpyDeviceToDevice, f->stream));
-  std::vector<double> a(L, 0.0), w0(L, 0.0), wy_old(L, 0.0), wyv(L, 0.0);
-  for (int col = 0; col < L; ++col) a[col] = -1.0;
+  std::vector<double> a(L, -1.0);
   set_coef(f, a, L);
   axpy(f, nl, L, f->q, f->r);
   project(f, f->r, f->w, L);
-  FTRY(dots(f, f->nlam, L, f->w, f->w));
-  std::vector<int> active(L, 0), its(L, 0);
-  for (int col = 0; col < L; ++col) {
-    w0[col] = std::sqrt(f->h_dots[col]);
-    active[col] = col < nrhs && w0[col] > 0.0;
-  }
-  bool any = false;
-  for (int col = 0; col < L; ++col) any |= active[col] != 0;
-  int it = 0;
-  while (any && it < max_it) {
-    // y = P M^-1 w; beta = (w.y) / (w.y)_old; p = y + beta p
+  const dim3 ge(std::min(4096u, grid_for(nl * L, 256)));
+  // y = P M^-1 w; beta = (w.y) / (w.y)_old; p = y + beta p.  Enqueued before the host
+  // waits for the stopping test in front of it (which leaves the GPU no gap): past
+  // the last iteration it is not used.
+  auto direction = [&](int it) {
     precond(f, f->w, f->y, L);
     project(f, f->y, f->y, L);
-    FTRY(dots(f, f->nlam, L, f->w, f->y));
-    for (int col = 0; col < L; ++col) {
-      wyv[col] = f->h_dots[col];
-      a[col] = (it == 0 || !active[col]) ? 0.0 : wyv[col] / wy_old[col];
-    }
-    set_coef(f, a, L);
-    if (it == 0) FHIP(hipMemsetAsync(f->p, 0, nl * L * sizeof(double), f->stream));
-    xpay(f, nl, L, f->y, f->p);
+    feti_dot(f, kFetiBeta, it, tol, L, nrhs, f->w, f->y);
+    hipLaunchKernelGGL(k_feti_direction, ge, dim3(256), 0, f->stream, nl, L, it == 0 ? 1 : 0, f->y, f->st, f->p);
+  };
+  const FetiHost &h = *f->h_st;
+  feti_dot(f, kFetiStart, 0, tol, L, nrhs, f->w, f->w);
+  FHIP(hipEventRecord(f->ev, f->stream));
+  direction(0);
+  FHIP(hipGetLastError());
+  FHIP(hipEventSynchronize(f->ev));
+  for (int it = 0; h.any && it < max_it;) {
     // q = F p; alpha = (w.y) / (p.q)
     fapply(f, f->p, f->q, L);
-    FTRY(dots(f, f->nlam, L, f->p, f->q));
-    for (int col = 0; col < L; ++col) {
-      const double pq = f->h_dots[col];
-      if (active[col] && !(pq > 0.0)) return ffail(f, DD_ENOTSPD, "FETI breakdown: p^T F p <= 0");
-      a[col] = active[col] ? wyv[col] / pq : 0.0;
-      wy_old[col] = wyv[col];
-    }
-    set_coef(f, a, L);
-    axpy(f, nl, L, f->p, f->lam);
-    for (int col = 0; col < L; ++col) a[col] = -a[col];
-    set_coef(f, a, L);
-    axpy(f, nl, L, f->q, f->r);
+    feti_dot(f, kFetiAlpha, it, tol, L, nrhs, f->p, f->q);
+    hipLaunchKernelGGL(k_feti_update, ge, dim3(256), 0, f->stream, nl, L, f->p, f->q, f->st, f->lam, f->r);
     project(f, f->r, f->w, L);
-    FTRY(dots(f, f->nlam, L, f->w, f->w));
     ++it;
-    any = false;
-    for (int col = 0; col < L; ++col)
-      if (active[col]) {
-        its[col] = it;
-        if (std::sqrt(f->h_dots[col]) <= tol * w0[col]) active[col] = 0;
-        any |= active[col] != 0;
-      }
+    feti_dot(f, kFetiCheck, it, tol, L, nrhs, f->w, f->w);
+    FHIP(hipEventRecord(f->ev, f->stream));
+    if (it < max_it) direction(it);
+    FHIP(hipGetLastError());
+    FHIP(hipEventSynchronize(f->ev));
+    if (h.broken) {
+      FHIP(hipStreamSynchronize(f->stream));
+      return ffail(f, DD_ENOTSPD, "FETI breakdown: p^T F p <= 0");
+    }
   }
+  std::vector<int> active(h.active, h.active + L), its(h.its, h.its + L);
   // alpha = (G^T G)^-1 G^T (d - F lambda) (eq. forAlpha); u_U = S^+ (f - B^T lambda) - Z alpha (eq. forU)
   fapply(f, f->lam, f->q, L);
-  for (int col = 0; col < L; ++col) a[col] = -1.0;
   set_coef(f, a, L);
   FHIP(hipMemcpyAsync(f->r, f->d, nl * L * sizeof(double), hipMemcpyDeviceToDevice, f->stream));
   axpy(f, nl, L, f->q, f->r);
@@ -1242,6 +1424,8 @@ const char *dd_feti_last_error(const dd_feti_ctx *f) { return f ? f->err.c_str()
 void dd_feti_destroy(dd_feti_ctx *f) {
   if (!f) return;
   if (f->h_dots) (void)hipHostFree(f->h_dots);
+  if (f->h_st) (void)hipHostFree(f->h_st);
+  if (f->ev) (void)hipEventDestroy(f->ev);
   dd_destroy(f->D);
   dd_destroy(f->P);
   delete f;
