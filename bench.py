@@ -63,12 +63,12 @@ WORKLOADS = {
 # reported as null once that source changes.
 MEASURED_TRAFFIC = {
     # 2D peridynamics h = 1/160, 32 rhs: medians over the CG iterations' launches
-    "k_tile_rows<double,2,true>": dict(src="dd_tiles.h", sha="7e9d81ffc6acec94", workload="cfg4",
-                                       fetch_kib=160066.1, write_kib=9624.3,
-                                       fetch_scale=262144.0 / 131086.8, write_scale=262144.0 / 262146.9),
-    "k_tile_rows<float,2,true>": dict(src="dd_tiles.h", sha="7e9d81ffc6acec94", workload="cfg4",
-                                      fetch_kib=82966.3, write_kib=9624.3,
-                                      fetch_scale=262144.0 / 131086.8, write_scale=262144.0 / 262146.9),
+    "k_tile_rows<double,2,true>": dict(src="dd_tiles.h", sha="02ab92cc039c0347", workload="cfg4",
+                                       fetch_kib=120536.8, write_kib=9969.2,
+                                       fetch_scale=262144.0 / 131087.2, write_scale=262144.0 / 262144.4),
+    "k_tile_rows<float,2,true>": dict(src="dd_tiles.h", sha="02ab92cc039c0347", workload="cfg4",
+                                      fetch_kib=66503.3, write_kib=9969.2,
+                                      fetch_scale=262144.0 / 131087.2, write_scale=262144.0 / 262144.4),
 }
 
 
@@ -492,17 +492,6 @@ def solve_leg(dd, torch, wl, b, tol, steps, warmup, launch, workload):
     return out, sols
 
 
-# FP64 vector peak (256 CUs at 2.4 GHz) for the ALU-bound assembly kernel
-FP64_VECTOR_PEAK_TFLOPS = 78.6
-# FP64 operations per quadrature-point pair of the constant kernel (whose
-# value does not depend on the points; the rule weights of the two elements,
-# the areas and the constant are combined once per point of F): d_m (1 sub),
-# the pair weight (1 mul) times d_m (1 mul), and per vertex of the union of a
-# pair without shared vertices (6): d_n (1 sub, E's three vertices only) and
-# the accumulation (1 fma: 2)
-ASM_FLOPS_PER_QP = 18
-
-
 def interacting_pairs_per_row(spec) -> int:
     """Ordered element pairs (E holding the node, F) that pass the barycentre
     test, for a free node whose partners all lie on the mesh (the collar is
@@ -538,7 +527,7 @@ def assembly_leg(dd, workloads, torch, reps=5):
     """Device assembly (dd_assemble_2d) of the benchmark system's stiffness
     windows (2D constant kernel, h = 1/128, delta = 0.1, 16 129 rows of 31 x
     31) against the CPU generator on the host's cores: time, agreement, and
-    the FP64 vector rate of the quadrature (ALU-bound)."""
+    the rate at which the windows are written."""
     import numpy as np
     spec = workloads.spec_2d_const()
     R = workloads.window_radius(spec)
@@ -562,14 +551,15 @@ def assembly_leg(dd, workloads, torch, reps=5):
     ref = ref.reshape(rows, -1)
     err = float((np.abs(got - ref) / np.abs(ref).max(axis=1, keepdims=True)).max())
     pairs = interacting_pairs_per_row(spec) * rows
-    qp = pairs * 49
-    tflops = qp * ASM_FLOPS_PER_QP / (ms * 1e-3) / 1e12
+    # the windows written once: with the mesh uniform one row is integrated and
+    # copied to all of them
+    nbytes = 8.0 * rows * W * W
+    ach = nbytes / (ms * 1e-3) / 1e9
     return dict(system="2d-const h=1/128 delta=0.1", rows=rows, window=f"{W}x{W}", ms=ms,
                 cpu_generator_ms=cpu_ms, cpu_threads=workloads._nthreads(), speedup=cpu_ms / ms,
-                max_rel_diff_vs_generator=err, element_pairs=pairs, quad_pairs=qp,
-                roofline=dict(bound="alu", achieved=tflops, peak=FP64_VECTOR_PEAK_TFLOPS, unit="TFLOP/s",
-                              frac=tflops / FP64_VECTOR_PEAK_TFLOPS,
-                              flops_per_quad_pair=ASM_FLOPS_PER_QP))
+                max_rel_diff_vs_generator=err, element_pairs=pairs, quad_pairs=pairs * 49,
+                roofline=dict(bound="hbm", achieved=ach, peak=HBM_PEAK_GBS, unit="GB/s",
+                              frac=ach / HBM_PEAK_GBS, algo_bytes=nbytes))
 
 
 def jacobi_cg_leg(dd, workloads, wl, b, tol, steps, warmup, torch):

@@ -100,7 +100,10 @@ typedef enum {
  * update).  Untuned solves use three when the explicit inverse is applied and
  * subdomains exist, at every batch width (a column's result does not depend on
  * the batch); the autotuner times both forms per width.  The persistent
- * kernel, the triangular-sweep variant and the batch API use four. */
+ * kernel, the triangular-sweep variant and the batch API use four.  Interfaces
+ * of at most 384 unknowns (with at most 7680 interior ones) solve FP64 and mixed
+ * loads under DD_LAUNCH_AUTO in one launch on S formed as a dense matrix, unless
+ * gather32 is on or an autotuned schedule for the width says otherwise. */
 typedef enum {
   DD_LAUNCH_AUTO = 0,
   DD_LAUNCH_KERNELS = 1,     /* one kernel launch per phase, host polls convergence */
@@ -127,9 +130,9 @@ typedef struct {
                             they multiply (half the gathered bytes; pays off for wide
                             batches): -1 = automatic (dd_solve: the autotuned schedule, else
                             off; batches: off), 0 = off, 1 = on */
-  int32_t tiles;         /* batches of 8 or more columns: coupling products on 16x16 tiles and
-                            interior solves on the matrix cores (the direction kept by its own
-                            kernel); a column's result then differs in rounding from the
+  int32_t tiles;         /* batches of 8 or more columns: coupling products on units of 16 rows x
+                            16 listed columns and interior solves on 16x16 tiles, both on the
+                            matrix cores (the direction kept by its own kernel); a column's result then differs in rounding from the
                             narrow-batch kernels but does not depend on the width among 8..64:
                             -1 = automatic (the autotuned schedule, else off), 0 = off,
                             1 = on (ignored below 8 columns, with the triangular-sweep apply,
@@ -251,7 +254,8 @@ dd_status dd_get_schur_diag(dd_ctx *ctx, dd_precision prec, double *out);
 /* Schedule chosen by the autotuner (dd_autotune). */
 typedef struct {
   int32_t apply;             /* dd_apply */
-  int32_t launch;            /* dd_launch */
+  int32_t launch;            /* dd_launch (DD_LAUNCH_PERSISTENT also for the one launch of
+                                small interfaces) */
   int32_t direction_kernel;  /* 1: direction kept in memory by its own kernel, 0: formed on the fly */
   int32_t check_every;       /* polling lag (kernels) or iterations per graph (graph) */
   double ms_per_solve;       /* measured time of one solve of the batch with this schedule */
@@ -296,7 +300,8 @@ enum { DD_SLOT_FREE = 0, DD_SLOT_RUNNING = 1, DD_SLOT_DONE = 2, DD_SLOT_FALLBACK
 
 /* Open a batch: precision and tolerances (opts) for every slot.  With
  * DD_MIXED and opts->gather32 == 1 the session keeps the direction in memory
- * and its FP32-data products gather FP32 vector copies; apply, launch and
+ * and its FP32-data products gather FP32 vector copies (contexts set up for 8 or
+ * more columns run them on the matrix cores at every width); apply, launch and
  * check_every are not used (every step launches its kernels directly). */
 dd_status dd_batch_begin(dd_ctx *ctx, dd_precision prec, const dd_solve_opts *opts);
 

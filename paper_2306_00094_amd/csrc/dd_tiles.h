@@ -122,8 +122,8 @@ __global__ void k_units_to_f32(size_t nunit, const double *__restrict__ in, floa
 // NCB >= 2) lane l holds the NCB consecutive columns NCB (l % 16) + q, q < NCB,
 // of each row it reads, so that one 16- or 32-byte load brings all of them
 // (the q-th matrix instruction then computes the columns NCB j + q, j < 16).
-// For NCB = 1 lane l holds column l % 16; at ld = 8 the lanes of columns
-// 8..15 read columns 0..7 again (their products land in output columns that
+// For NCB = 1 lane l holds column l % 16; below ld = 16 the lanes past the last
+// column read the columns again (their products land in output columns that
 // are not stored).
 template <int NCB>
 __device__ __forceinline__ int slice_col0(int l16, int ld) {
@@ -173,9 +173,10 @@ __device__ __forceinline__ void unit_a(const float *unit, int lane, float (&a)[4
 // added to the FP64 accumulators, so FP32 rounding enters only within them
 // (rows are then in the FP32 instruction's order: row 4 (l / 16) + r of lane l,
 // register r).  WIDE: FP32 units and vector rows are widened and run on the FP64
-// instruction (every product and sum in FP64).  A pass of the loop runs unit j while the
-// operands of units j + 1 .. j + D - 1 and the column lists of the D after them
-// are in flight.  Scheduling barriers keep every group of loads in program
+// instruction (every product and sum in FP64; the four-launch iteration, whose CSR
+// rows hold them in FP64 too).  A pass of the loop runs unit j while the operands
+// of units j + 1 .. j + D - 1 and the column lists of the D after them are in
+// flight.  Scheduling barriers keep every group of loads in program
 // order, so that the instructions of one buffer wait only for that buffer's
 // loads; the loads past a wave's last unit are skipped.
 template <int NCB, int D, bool WIDE, typename VT, typename XT>
@@ -298,7 +299,7 @@ constexpr int kTW = 4;
 // without the unit and vector loads, matrix instructions and the fixed work of a
 // block (column lists, wave sums, dot product) take 50 of the 66 us in FP64,
 // 14 us of it fixed; the units are 215 MB.  32-row blocks of aligned 8-column
-// units took 78.6 us (FP64) and 56 us (FP32, now 47).  Waves per block (2, 4, 8)
+// units took 78.6 us (FP64) and 56 us (FP32, now 45).  Waves per block (2, 4, 8)
 // and units in flight (1 to 4) change it by less than 5 % around 4 and 2.
 // run (may be nullptr): the CG loop's flag of columns still
 // iterating; when it reads 0 the launch does nothing (the loop's host runs a
