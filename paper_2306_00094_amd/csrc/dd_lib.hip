@@ -120,7 +120,8 @@ struct dd_ctx {
   double *d_kii_t = nullptr;          // K_II packed into tiles (FP64 residual of the mixed path)
   double *d_ig_val64 = nullptr, *d_g_val64 = nullptr, *d_kii64 = nullptr;
   Ops op[2];
-  Work w{};
+  Work w{}, w0{};          // work vectors; w0: as allocated, which captured graphs address (sessions
+                           // exchange the pointers of w and give them back when they end)
   ColState st{};
   StateBlock *d_state = nullptr;
   RedBuf red{};
@@ -2089,6 +2090,7 @@ dd_status dd_setup(const dd_problem *p, void *hip_stream, int32_t max_nrhs, dd_c
     StateBlock *sb = c->d_state;
     w.bnrm2 = sb->bnrm2;
     w.rnrm2 = sb->rnrm2;
+    c->w0 = w;
     c->st.rz = sb->rz;
     c->st.alpha = sb->alpha;
     c->st.beta = sb->beta;
@@ -2454,6 +2456,7 @@ dd_status dd_batch_end(dd_ctx *c) {
   if (!c) return fail(nullptr, DD_EINVAL, "ctx is NULL");
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->batch.on = false;
+  c->w = c->w0;
   HIPCHK(c, hipMemsetAsync(c->st.active, 0, kMaxLd * sizeof(int), c->stream));
   return DD_OK;
 }
