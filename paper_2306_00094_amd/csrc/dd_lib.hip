@@ -95,7 +95,7 @@ struct dd_ctx {
   long long vpack = 0;
   int nloc = 0, n_wsq = 0;
   long long *d_vpos = nullptr, *d_voff = nullptr;
-  int *d_goff = nullptr, *d_dptr = nullptr, *d_dent = nullptr;
+  int *d_goff = nullptr, *d_dptr = nullptr, *d_dent = nullptr, *d_gcol = nullptr;   // d_gcol: g_map, all subdomains
   int4 *d_wsq_items = nullptr;
   double *d_kgg_diag = nullptr;
   int *d_ni = nullptr, *d_ioff = nullptr, *d_rowsub = nullptr, *d_imap = nullptr,
@@ -150,6 +150,7 @@ struct dd_ctx {
   Gather32 g32{};             // FP32 gather copies of the three-launch iteration being launched
   int *d_flow = nullptr;      // single-launch Cholesky: ticket, timeout
   double *fac_x = nullptr, *fac_packed = nullptr, *fac_dloc = nullptr;   // factor work space
+  double *direct_t = nullptr; // K_II^{-1} K_IG (NI rows), from which the dense S is formed
   bool packed_ready = false;
   int num_cu = 0;
   size_t max_lds = 65536;     // LDS bytes one workgroup may use
@@ -429,7 +430,7 @@ size_t footprint_bytes(const dd_problem *p, dd_precision prec, int max_nrhs) {
     if (prec == DD_MIXED) b += kp * 8;  // the FP64 fallback's packed inverse
   }
   if (p->n_sub > 0 && p->n_gamma <= kDirectMax && NI <= (size_t)kDirectMaxNI)     // dense S of a small interface
-    b += (size_t)p->n_gamma * direct_ld(p->n_gamma) * 8 * (prec == DD_MIXED ? 2 : 1);
+    b += ((size_t)p->n_gamma * (prec == DD_MIXED ? 2 : 1) + NI) * direct_ld(p->n_gamma) * 8;
   b += (12 * (size_t)p->n_gamma + 6 * NI) * ld * 8;                   // work vectors
   b += (4 * (size_t)p->n_gamma + NI) * ld * 4;                        // FP32 gather copies
   size_t chunks = std::max<size_t>((p->n_gamma + kGChunk - 1) / kGChunk,
@@ -1064,7 +1065,8 @@ dd_status factor_impl(dd_ctx *c, int pi) {
 
 // The one-launch CG on the dense S (dd_direct.h) serves this system.
 bool can_direct(const dd_ctx *c) {
-  return c->n_gamma > 0 && c->n_gamma <= kDirectMax && c->NI > 0 && c->NI <= kDirectMaxNI && !c->classic_cg;
+  return c->n_gamma > 0 && c->n_gamma <= kDirectMax && c->NI > 0 && c->NI <= kDirectMaxNI && !c->classic_cg &&
+         c->use_mfma;
 }
 
 dd_status ensure_ops(dd_ctx *c, int pi) {
@@ -1085,7 +1087,14 @@ dd_status ensure_ops(dd_ctx *c, int pi) {
   TRY(al((void **)&o.diag, c->n_gamma * 8));
   TRY(al((void **)&o.dinv, c->n_gamma * 8));
   if (c->tiles) TRY(al(&o.kinv_t, (size_t)c->t_kpack * s));
-  if (can_direct(c)) TRY(al((void **)&o.sd, (size_t)c->n_gamma * direct_ld(c->n_gamma) * 8));
+  if (can_direct(c)) {
+    TRY(al((void **)&o.sd, (size_t)c->n_gamma * direct_ld(c->n_gamma) * 8));
+    if (!c->direct_t) {                // columns a subdomain does not couple to stay zero
+      const size_t nt = (size_t)c->NI * direct_ld(c->n_gamma) * 8;
+      TRY(al((void **)&c->direct_t, nt));
+      HIPCHK(c, hipMemsetAsync(c->direct_t, 0, nt, c->stream));
+    }
+  }
   if (pi == DD_FP64) {
     o.ig_val = c->d_ig_val64;
     o.g_val = c->d_g_val64;
@@ -1204,15 +1213,18 @@ dd_status direct_cg(dd_ctx *c, int prec, int ld, int nrhs, const CoreOpts &o, do
   Ops &op = c->op[prec];
   const int N = c->n_gamma, Np = direct_ld(N);
   if (!op.sd_ready) {
-    const size_t lds = (size_t)c->NI * sizeof(double);
-    if (prec == DD_FP64)
-      hipLaunchKernelGGL((k_direct_schur<double, double>), dim3(N), dim3(kSchurBlock), lds, c->stream, N, Np, c->NI,
-                         c->d_g_ptr, c->d_g_split, c->d_g_col, (const double *)op.g_val, (const double *)op.kinv,
-                         c->d_koff, c->d_ioff, c->d_ni, c->d_rowsub, op.sd);
-    else
-      hipLaunchKernelGGL((k_direct_schur<float, float>), dim3(N), dim3(kSchurBlock), lds, c->stream, N, Np, c->NI,
-                         c->d_g_ptr, c->d_g_split, c->d_g_col, (const float *)op.g_val, (const float *)op.kinv,
-                         c->d_koff, c->d_ioff, c->d_ni, c->d_rowsub, op.sd);
+    const dim3 gt(c->n_wsq, grid_for((c->max_ni + 15) / 16, kWavesPerBlock));
+    auto form = [&](auto v) {
+      typedef decltype(v) T;
+      if (c->n_wsq > 0)
+        hipLaunchKernelGGL(k_direct_columns<T>, gt, dim3(kBlock), 0, c->stream, (const T *)op.kinv, c->fac_packed,
+                           c->d_koff, c->d_voff, c->d_ni, c->d_goff, c->d_ioff, c->d_wsq_items, c->d_gcol, Np,
+                           c->direct_t);
+      hipLaunchKernelGGL(k_direct_schur<T>, dim3(Np), dim3(kSchurBlock / Np * Np), 0, c->stream, N, Np, c->d_g_ptr,
+                         c->d_g_split, c->d_g_col, (const T *)op.g_val, c->direct_t, op.sd);
+    };
+    if (prec == DD_FP64) form(0.0);
+    else form(0.0f);
     HIPCHK(c, hipGetLastError());
     op.sd_ready = true;
   }
@@ -1971,6 +1983,8 @@ dd_status dd_setup(const dd_problem *p, void *hip_stream, int32_t max_nrhs, dd_c
       for (int k = 0; k < c->n_sub; ++k)
         for (int jl = 0; jl < p->sub[k].n_g; ++jl) dent[fill[p->sub[k].g_map[jl]]++] = goff[k] + jl;
     }
+    std::vector<int> gcol;
+    for (int k = 0; k < c->n_sub; ++k) gcol.insert(gcol.end(), p->sub[k].g_map, p->sub[k].g_map + p->sub[k].n_g);
     std::vector<double> kd(c->n_gamma, 0.0);
     for (int j = 0; j < c->n_gamma; ++j)
       for (int a = p->kgg_rowptr[j]; a < p->kgg_rowptr[j + 1]; ++a)
@@ -1982,6 +1996,7 @@ dd_status dd_setup(const dd_problem *p, void *hip_stream, int32_t max_nrhs, dd_c
     if ((s = upload(c, &c->d_voff, voff.data(), voff.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_goff, goff.data(), goff.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_wsq_items, items.data(), items.size())) != DD_OK) return bail(s);
+    if ((s = upload(c, &c->d_gcol, gcol.data(), gcol.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_dptr, dptr.data(), dptr.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_dent, dent.data(), dent.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_kgg_diag, kd.data(), kd.size())) != DD_OK) return bail(s);
