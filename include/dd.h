@@ -257,8 +257,8 @@ dd_status dd_get_schur_diag(dd_ctx *ctx, dd_precision prec, double *out);
 /* Schedule chosen by the autotuner (dd_autotune). */
 typedef struct {
   int32_t apply;             /* dd_apply */
-  int32_t launch;            /* dd_launch (DD_LAUNCH_PERSISTENT also for the one launch of
-                                small interfaces) */
+  int32_t launch;            /* dd_launch (DD_LAUNCH_AUTO: the one launch of small interfaces,
+                                which AUTO solves of such a context run) */
   int32_t direction_kernel;  /* 1: direction kept in memory by its own kernel, 0: formed on the fly */
   int32_t check_every;       /* polling lag (kernels) or iterations per graph (graph) */
   double ms_per_solve;       /* measured time of one solve of the batch with this schedule */

@@ -156,7 +156,6 @@ struct dd_ctx {
   size_t max_lds = 65536;     // LDS bytes one workgroup may use
   unsigned *d_bar = nullptr;  // persistent-launch barrier: count, generation, abort
   long long spin_limit = 1ll << 20;
-  int last_launch = DD_LAUNCH_KERNELS;
   struct GraphEntry {
     int prec, ld, apply, precond, dk, iters, cg3;
     double *x;
@@ -1384,7 +1383,6 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
   }
   if (o.direct) {
     c->tev_cg3_ld = 0;
-    c->last_launch = DD_LAUNCH_PERSISTENT;
     TRY(direct_cg(c, prec, ld, nrhs, o, uG));
     kig_apply(c, prec, plain(uG), ld, bI, -1.0, w.yI);
     interior_solve(c, prec, o.apply, w.yI, uI, ld);
@@ -1438,13 +1436,11 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
     HIPCHK(c, hipMemcpyAsync(&abort_flag, c->d_bar + 2, sizeof(unsigned), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (abort_flag) return fail(c, DD_EHIP, "persistent CG kernel aborted: a grid barrier wait exceeded its limit");
-    c->last_launch = DD_LAUNCH_PERSISTENT;
     kig_apply(c, prec, plain(uG), ld, bI, -1.0, w.yI);
     interior_solve(c, prec, o.apply, w.yI, uI, ld);
     HIPCHK(c, hipGetLastError());
     return DD_OK;
   }
-  c->last_launch = DD_LAUNCH_KERNELS;
   // host polling with a lag: iteration `it` writes h_nact[it % nslots] = active + 1
   const int lag = std::min(8, std::max(1, o.check_every > 0 ? o.check_every : 2));
   std::vector<int> ring_it(c->nslots, -1);
@@ -1600,7 +1596,6 @@ dd_status core_solve(dd_ctx *c, int prec, const double *bI, const double *bG, do
         if (((volatile int *)c->h_nact)[0] == 1) break;
       }
     }
-    c->last_launch = DD_LAUNCH_GRAPH;
   } else {
     // The update kernel of iteration `it` stores (active columns + 1) into
     // host memory h_nact[it % nslots]; the host waits for that value of
@@ -2277,7 +2272,7 @@ dd_status dd_autotune(dd_ctx *c, dd_precision prec, int32_t nrhs, const dd_solve
       cands.push_back({DD_APPLY_INV, DD_LAUNCH_GRAPH, 1, 4, 4});
     }
   }
-  if (can_direct(c))       // one launch runs the whole CG (reported as a persistent launch)
+  if (can_direct(c))       // one launch runs the whole CG
     cands.push_back({DD_APPLY_INV, DD_LAUNCH_AUTO, 0, 0, 0, 0.0, true});
   cands.push_back({DD_APPLY_TRSM, DD_LAUNCH_KERNELS, 0, 2, 0});
   // The cooperative persistent launch is timed only on request
@@ -2361,7 +2356,7 @@ dd_status dd_autotune(dd_ctx *c, dd_precision prec, int32_t nrhs, const dd_solve
   t.inner_tol = prec == DD_MIXED ? best_itol : 0.0;
   if (out) {
     out->apply = bc.apply;
-    out->launch = bc.direct ? DD_LAUNCH_PERSISTENT : bc.launch;
+    out->launch = bc.launch;      // (the one-launch CG: AUTO, which selects it)
     out->direction_kernel = bc.dk;
     out->check_every = bc.ce;
     out->ms_per_solve = best;
