@@ -673,11 +673,13 @@ void gamma_apply(dd_ctx *c, int prec, Src p, const double *z, int ld, const doub
 // (batches of kTileMinLd or more columns; dd_tiles.h)
 // Whether the interface rows sum p^T q by groups of row blocks (a completion
 // count per group) or leave the block sums to the update, whose every workgroup
-// then reads them all.
-#ifndef DD_DG
-#define DD_DG 640
-#endif
-inline int dot_grouped(int nrb) { return nrb > DD_DG; }
+// then reads them all.  8 and 32 columns, block sums against groups (us a solve):
+// 122 blocks 750 / 826 and 979 / 1 084, 324 blocks 1 129 / 1 160 and 1 496 / 1 579,
+// 588 blocks 1 941 / 1 978 and 2 567 / 2 584, 679 blocks 3 891 / 3 884 and 5 192 /
+// 5 373, 1 086 blocks 6 173 / 5 905 and 8 129 / 7 925, 2 320 blocks 11 839 / 11 222
+// and 16 431 / 15 441.
+constexpr int kDotBlocks = 640;
+inline int dot_grouped(int nrb) { return nrb > kDotBlocks; }
 
 template <typename VT, int NCB, bool DOT, bool WIDE>
 void launch_tile_rows_t(dd_ctx *c, bool interface_rows, const VT *val, const double *x1,
@@ -766,9 +768,12 @@ void dense_tiles(dd_ctx *c, int prec, bool kii, const double *y, int ld, const d
 // Rows of a slab of the tiled CG's update: its partial sums are read by every
 // workgroup of the direction launch, so large interfaces take large slabs (the
 // peridynamic system's 37 114 rows: 290 slabs of 128); small ones take small
-// slabs, so that the launch fills the chip (5 181 rows: 162 slabs of 32).  The
-// rule looks at the interface only: a column's sums must not depend on the
-// batch.
+// slabs, so that the launch fills the chip (5 181 rows: 162 slabs of 32).  Slabs of
+// 32, 64 and 128 rows, us a solve of 8 and of 32 columns: 5 181 rows 1 141 / 1 156 /
+// 1 165 and 1 512 / 1 486 / 1 504, 9 405 rows 1 947 / 1 945 / 1 993 and 2 610 / 2 578 /
+// 2 565, 17 370 rows 6 036 / 5 970 / 5 963 and 8 530 / 7 987 / 7 934, 37 114 rows
+// 11 393 / 11 246 / 11 159 and 16 480 / 15 516 / 15 468.  The rule looks at the
+// interface only: a column's sums must not depend on the batch.
 inline int tile_slab(int n_gamma) { return n_gamma >= 32768 ? 128 : (n_gamma >= 8192 ? 64 : 32); }
 
 // The update of a tiled CG step (k_tile_update): mode 1 the step (xup: also x),
