@@ -1184,7 +1184,8 @@ dd_status dd_feti_solve(dd_feti_ctx *f, const double *b_dev, double *u_dev, int3
   const dim3 ge(std::min(4096u, grid_for(nl * L, 256)));
   // y = P M^-1 w; beta = (w.y) / (w.y)_old; p = y + beta p.  Enqueued before the host
   // waits for the stopping test in front of it (which leaves the GPU no gap): past
-  // the last iteration it is not used.
+  // the last iteration it is not used (a solve of zero loads, which has none, takes
+  // 7 to 16 us more for it, 0.23 ms at h = 1/64).
   auto direction = [&](int it) {
     precond(f, f->w, f->y, L);
     project(f, f->y, f->y, L);

@@ -2216,7 +2216,7 @@ k_potrf_panel(T *__restrict__ blocks, const long long *__restrict__ koff,
 //
 // Workgroups take tickets t = J * n_sub + k in the order they start, so a
 // workgroup only ever waits for block columns of smaller tickets, which have
-// already started: the waits cannot deadlock whatever the residency.  A
+// already started: the waits cannot deadlock whatever the residency.
 // The factor goes to its own buffer, which the host sets to all ones before the
 // launch (a NaN that arithmetic does not produce): a tile is ready once none of
 // its values is all ones, so the values are their own flags.  They are written

@@ -897,9 +897,9 @@ void launch_cg_dense(dd_ctx *c, const MT *kinv, int mode, int par, int ld, int n
 // ---------------------------------------------------------------- factor --
 // Single-launch left-looking Cholesky for blocks of up to 16 * 4 * 16 rows
 // (row tiles per wave held in registers: the smallest OWN >= ceil(tiles / 4)).
-// Returns false (nothing launched) when the blocks are larger.
+constexpr int kFlowRows = 16 * 4 * 16;
 template <typename T>
-bool launch_potrf_flow(dd_ctx *c, T *L, T *Xd) {
+void launch_potrf_flow(dd_ctx *c, T *L, T *Xd) {
   const int ntmax = (c->max_ni + 15) / 16, need = (ntmax + 3) / 4;
   const dim3 grid((unsigned)(c->n_sub * ntmax)), blk(kBlock);
   unsigned *ticket = (unsigned *)c->d_flow;
@@ -913,10 +913,8 @@ bool launch_potrf_flow(dd_ctx *c, T *L, T *Xd) {
   else if (need <= 8) DD_FLOW(8);
   else if (need <= 10) DD_FLOW(10);
   else if (need <= 12) DD_FLOW(12);
-  else if (need <= 16) DD_FLOW(16);
-  else return false;
+  else DD_FLOW(16);
 #undef DD_FLOW
-  return true;
 }
 
 template <typename T>
@@ -941,17 +939,17 @@ dd_status factor_impl(dd_ctx *c, int pi) {
   }
   T *X = mfma_inv ? (T *)c->fac_x : nullptr;
   if (c->n_sub > 0) HIPCHK(c, hipMemsetAsync(c->d_status, 0, c->n_sub * sizeof(int), c->stream));
-  bool flow = false;
-  if (c->use_mfma && c->n_sub > 0 && !c->panel_potrf) {
+  const bool flow = c->use_mfma && c->n_sub > 0 && !c->panel_potrf && c->max_ni <= kFlowRows;
+  if (flow) {
     // one launch; it also writes the diagonal blocks of X
     HIPCHK(c, hipMemsetAsync(c->d_flow, 0, 2 * sizeof(int), c->stream));
     HIPCHK(c, hipMemsetAsync(L, 0xff, n * sizeof(T), c->stream));
-    flow = launch_potrf_flow<T>(c, L, panel_trtri ? X : nullptr);
+    launch_potrf_flow<T>(c, L, panel_trtri ? X : nullptr);
     HIPCHK(c, hipGetLastError());
-  }
-  if (!flow) {
-    // K_II copied (and converted) into the factor buffer, then panel by panel: the diagonal block and the rows below it (one workgroup per
-    // subdomain), then the trailing update of all subdomains' tiles
+  } else {
+    // K_II copied (and converted) into the factor buffer, then panel by panel: the
+    // diagonal block and the rows below it (one workgroup per subdomain), then the
+    // trailing update of all subdomains' tiles
     if (pi == DD_FP64)
       hipLaunchKernelGGL((k_copy<double>), dim3(1024), dim3(256), 0, c->stream, n, c->d_kii64, (double *)L);
     else
@@ -1310,12 +1308,14 @@ bool use_tiles(const dd_ctx *c, int sched, int ld, int apply, int launch) {
 // Whether a solve runs the four-launch iteration with FP32 gathers on the units
 // (schur_units), as mixed sessions of the batch API with gather32 do in contexts
 // that have units: at every width, since a column's result must not depend on the
-// batch.  One column in a context of 16 takes 2.35 ms on the CSR rows and 2.31 ms on
-// the units for the constant kernel at h = 1/96, 4.15 and 4.2 ms for the fractional
-// one at h = 1/72, 8.6 and 7.4 ms for peridynamics at h = 1/120; 16 columns 6.2 and
-// 3.0 ms, 10.5 and 5.4 ms, 31.7 and 11.6 ms.  (Without FP32 gathers it would: the CSR rows form the direction as they
-// gather it, the units need the direction launch.  One FP64 column, constant
-// kernel: 1.33 and 1.72 ms.)
+// batch.  One column in a context of 16 takes 2.39 ms on the CSR rows and on the
+// units for the constant kernel at h = 1/96, 4.10 and 4.14 ms for the fractional one
+// at h = 1/72 (in a context of 64 3.79 and 3.95 ms, the most one column loses), 8.4
+// and 7.1 ms for peridynamics at h = 1/120; 16 columns 6.2 and 3.1 ms, 10.9 and 5.8
+// ms, 31.7 and 11.7 ms.
+// Not without FP32 gathers: there the CSR rows form the direction as they gather it,
+// while the units need the direction launch (one FP64 column, constant kernel: 1.33
+// and 1.72 ms).
 bool units32(const dd_ctx *c, int prec, int sched, int ld, int apply, int launch) {
   return prec == DD_MIXED && (sched & 2) && c->direction_kernel && c->tiles && c->NI > 0 && c->n_gamma > 0 &&
          !((sched & 1) && !c->classic_cg) && apply != DD_APPLY_TRSM && launch != DD_LAUNCH_PERSISTENT &&
