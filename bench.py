@@ -63,12 +63,12 @@ WORKLOADS = {
 # reported as null once that source changes.
 MEASURED_TRAFFIC = {
     # 2D peridynamics h = 1/160, 32 rhs: medians over the CG iterations' launches
-    "k_tile_rows<double,2,true>": dict(src="dd_tiles.h", sha="02ab92cc039c0347", workload="cfg4",
-                                       fetch_kib=120536.8, write_kib=9969.2,
-                                       fetch_scale=262144.0 / 131087.2, write_scale=262144.0 / 262144.4),
-    "k_tile_rows<float,2,true>": dict(src="dd_tiles.h", sha="02ab92cc039c0347", workload="cfg4",
-                                      fetch_kib=66503.3, write_kib=9969.2,
-                                      fetch_scale=262144.0 / 131087.2, write_scale=262144.0 / 262144.4),
+    "k_tile_rows<double,2,true>": dict(src="dd_tiles.h", sha="418b195792030fc9", workload="cfg4",
+                                       fetch_kib=120538.0, write_kib=9969.2,
+                                       fetch_scale=262144.0 / 131086.7, write_scale=262144.0 / 262151.1),
+    "k_tile_rows<float,2,true>": dict(src="dd_tiles.h", sha="418b195792030fc9", workload="cfg4",
+                                      fetch_kib=66498.9, write_kib=9969.2,
+                                      fetch_scale=262144.0 / 131086.7, write_scale=262144.0 / 262151.1),
 }
 
 

@@ -328,13 +328,18 @@ dd_status dd_batch_retire(dd_ctx *ctx, const int32_t *slots, int32_t ncol, doubl
 dd_status dd_batch_end(dd_ctx *ctx);
 
 /* Per-phase kernel timing of the CG loop (diagnostic entry for profiling).
- * Phases: one launch each per CG iteration. */
+ * Phases: one launch each per CG iteration of the stream launches; graph replays,
+ * the persistent launch and the one launch of small interfaces (the default there)
+ * are whole loops and report DD_PHASE_LOOP alone.  In the tiled iteration of wide
+ * batches DD_PHASE_KIG is the launch that ends it (column state, beta, direction,
+ * x, and y = K_IG z for the next one) and DD_PHASE_UPDATE has alpha, r, z and the
+ * partial sums. */
 enum {
   DD_PHASE_KIG = 0,       /* y = K_IG p                        (all subdomains) */
   DD_PHASE_INTERIOR = 1,  /* w = K_II^{-1} y                   (all subdomains) */
   DD_PHASE_GAMMA = 2,     /* q = K_GG p - K_GI w, p^T q partials (interface rows) */
   DD_PHASE_UPDATE = 3,    /* alpha, x, r, z updates, r^T z, r^T r, beta, convergence */
-  DD_PHASE_LOOP = 4,      /* one graph replay or one persistent CG launch (whole iterations) */
+  DD_PHASE_LOOP = 4,      /* one graph replay, persistent launch or one-launch CG */
   DD_NPHASES = 5
 };
 

@@ -22,7 +22,7 @@
 //
 // Operator of the CG iteration these kernels serve: S p summed over
 // subdomains (eq. subSchurComplement, summed as in eq. SchurComplement),
-// y = K_IG p, w = K_II^-1 y, q = K_GG p - K_GI w.
+// y = K_IG z, w = K_II^-1 y + beta w_before (= K_II^-1 K_IG p), q = K_GG p - K_GI w.
 //
 // Per output column the arithmetic depends only on that column (the matrix
 // instructions compute each output element from its own row and column), so
