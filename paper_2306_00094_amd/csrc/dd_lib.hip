@@ -833,14 +833,17 @@ void launch_cg_kig_t(dd_ctx *c, const VT *val, int mode, int par, int ld, const 
                      const int *mask) {
   const unsigned nsl = grid_for(c->n_gamma, kRowsE);
   const unsigned g = nsl + grid_for(c->NI, kWavesPerBlock);
+  // iteration 0 has no p^T q yet (gamma_parts is still that of the solve before, which
+  // may count the block sums of the tiled rows, many more than part3 holds)
+  const int npq = mode == 0 ? 0 : c->gamma_parts;
   if (c->g32.z_old)
     hipLaunchKernelGGL((k_cg_kig<C, E, VT, true>), dim3(g), dim3(kBlock), 0, c->stream, mode, par, c->NI,
                        (int)nsl, c->d_ig_ptr, c->d_ig_col, val, c->n_gamma, ld, v, c->w.yI, c->red, c->st,
-                       mask, c->gamma_parts, c->g32);
+                       mask, npq, c->g32);
   else
     hipLaunchKernelGGL((k_cg_kig<C, E, VT>), dim3(g), dim3(kBlock), 0, c->stream, mode, par, c->NI,
                        (int)nsl, c->d_ig_ptr, c->d_ig_col, val, c->n_gamma, ld, v, c->w.yI, c->red, c->st,
-                       mask, c->gamma_parts, c->g32);
+                       mask, npq, c->g32);
 }
 
 template <typename VT>
