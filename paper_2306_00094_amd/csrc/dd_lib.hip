@@ -1093,11 +1093,13 @@ dd_status ensure_ops(dd_ctx *c, int pi) {
   TRY(al((void **)&o.dinv, c->n_gamma * 8));
   if (c->tiles) TRY(al(&o.kinv_t, (size_t)c->t_kpack * s));
   if (can_direct(c)) {
-    TRY(al((void **)&o.sd, (size_t)c->n_gamma * direct_ld(c->n_gamma) * 8));
-    if (!c->direct_t) {                // columns a subdomain does not couple to stay zero
-      const size_t nt = (size_t)c->NI * direct_ld(c->n_gamma) * 8;
-      TRY(al((void **)&c->direct_t, nt));
-      HIPCHK(c, hipMemsetAsync(c->direct_t, 0, nt, c->stream));
+    // S, and behind it K_II^{-1} K_IG (once per context; columns a subdomain does not
+    // couple to stay zero)
+    const size_t ns = (size_t)c->n_gamma * direct_ld(c->n_gamma), nt = (size_t)c->NI * direct_ld(c->n_gamma);
+    TRY(al((void **)&o.sd, (ns + (c->direct_t ? 0 : nt)) * 8));
+    if (!c->direct_t) {
+      c->direct_t = o.sd + ns;
+      HIPCHK(c, hipMemsetAsync(c->direct_t, 0, nt * 8, c->stream));
     }
   }
   if (pi == DD_FP64) {
@@ -1986,8 +1988,8 @@ dd_status dd_setup(const dd_problem *p, void *hip_stream, int32_t max_nrhs, dd_c
       for (int k = 0; k < c->n_sub; ++k)
         for (int jl = 0; jl < p->sub[k].n_g; ++jl) dent[fill[p->sub[k].g_map[jl]]++] = goff[k] + jl;
     }
-    std::vector<int> gcol;
-    for (int k = 0; k < c->n_sub; ++k) gcol.insert(gcol.end(), p->sub[k].g_map, p->sub[k].g_map + p->sub[k].n_g);
+    const size_t ndent = dent.size();          // behind them: g_map of all subdomains
+    for (int k = 0; k < c->n_sub; ++k) dent.insert(dent.end(), p->sub[k].g_map, p->sub[k].g_map + p->sub[k].n_g);
     std::vector<double> kd(c->n_gamma, 0.0);
     for (int j = 0; j < c->n_gamma; ++j)
       for (int a = p->kgg_rowptr[j]; a < p->kgg_rowptr[j + 1]; ++a)
@@ -1999,9 +2001,9 @@ dd_status dd_setup(const dd_problem *p, void *hip_stream, int32_t max_nrhs, dd_c
     if ((s = upload(c, &c->d_voff, voff.data(), voff.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_goff, goff.data(), goff.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_wsq_items, items.data(), items.size())) != DD_OK) return bail(s);
-    if ((s = upload(c, &c->d_gcol, gcol.data(), gcol.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_dptr, dptr.data(), dptr.size())) != DD_OK) return bail(s);
     if ((s = upload(c, &c->d_dent, dent.data(), dent.size())) != DD_OK) return bail(s);
+    c->d_gcol = c->d_dent + ndent;
     if ((s = upload(c, &c->d_kgg_diag, kd.data(), kd.size())) != DD_OK) return bail(s);
   }
   if ((s = upload(c, &c->d_imap, imap.data(), NI)) != DD_OK) return bail(s);
